@@ -228,6 +228,61 @@ def work(case):
     return {"bytes": elements * (2 * es + 2 * 8), "flops": 2 * 4.0 * elements * sum(_factors(c))}
 
 
+def exact(case, seed):
+    """What run() returns for these inputs, by torch's own 64-bit products and Fourier transforms."""
+    c, s = case, prepare(case, seed)
+    wide = lambda t: None if t is None else [wide(v) for v in t] if isinstance(t, list) else t.double()     # noqa: E731
+    s = {name: wide(v) if isinstance(v, (torch.Tensor, list)) else v for name, v in s.items()}
+
+    def product(x, R, L):
+        """P L P R P x over the last axis: blocks of R take every nb-th element, blocks of L the row-major middle."""
+        z = torch.einsum("krc,xck->xrk", R, x.reshape(-1, R.shape[2], R.shape[0]))
+        w = torch.einsum("jlc,xjc->xlj", L, z.reshape(-1, L.shape[0], L.shape[2]))
+        return w.reshape(*x.shape[:-1], -1)
+
+    def conv(u, k, g_in, g_out, nfft):
+        a = u if g_in is None else u * g_in
+        y = torch.fft.irfft(torch.fft.rfft(a, nfft) * torch.fft.rfft(k, nfft), nfft)[..., :u.shape[-1]]
+        return y if g_out is None else y * g_out
+
+    if c["kind"] == "product":
+        return product(s["x"], s["R"], s["L"])
+    if c["kind"] == "conv":
+        return conv(s["u"], s["k"], s["g_in"], s["g_out"], c["nfft"])
+    if c["kind"] == "mlp":
+        def layer(x, R, L):
+            if L is None:
+                return torch.einsum("krc,xkc->xkr", R, x.reshape(-1, R.shape[0], R.shape[2])).reshape(len(x), -1)
+            return product(x, R, L)
+        h = torch.nn.functional.gelu(layer(s["x"], s["W1_R"], s["W1_L"]) + s["b1"])
+        return layer(h, s["W2_R"], s["W2_L"]) + s["b2"]
+    if c["kind"] == "mixer_training":
+        names = {"du": s["u"], "dK": s["K"], "dg_in": s["g_in"], "dg_out": s["g_out"]}
+        names.update(zip(("dR1", "dL1", "dR2", "dL2"), s["matrices"]))
+        leaves = {name: t.requires_grad_() for name, t in names.items() if t is not None}
+        a = s["u"] if s["g_in"] is None else s["u"] * s["g_in"]
+        y = product(s["K"] * product(a, *s["matrices"][:2]), *s["matrices"][2:])
+        y = y if s["g_out"] is None else y * s["g_out"]
+        found = dict(zip(leaves, torch.autograd.grad(y, list(leaves.values()), s["dy"])))
+        return dict({name: found.get(name) for name in names}, y=y.detach())
+    if c["kind"] == "m2_layer":
+        mixed = product(torch.relu(s["n_kernel"] * product(s["x"].transpose(1, 2), *s["seq"][:2])), *s["seq"][2:]).transpose(1, 2)
+        out = product(torch.relu(s["d_kernel"] * product(mixed, *s["dim"][:2])), *s["dim"][2:])
+        return torch.nn.functional.layer_norm(out + mixed, (c["bd"] ** 2,), s["gamma"], s["beta"], 1e-5)
+    if c["kind"] == "hyena":
+        B, n, d, dh = c["B"], c["n"], c["d"], c["head_dim"]
+        p = (s["u"] @ s["W_in"].T + s["b_in"]).transpose(1, 2)
+        short = sum(torch.nn.functional.pad(p, (t, 0))[..., :n] * s["k_short"][:, t, None] for t in range(c["taps"]))
+        x1, x2, v = short.reshape(B, 3, d // dh, dh, n).unbind(1)
+        O = torch.zeros_like(v)
+        for i in range(dh):     # the head's i-th feature gates all of its d_h inputs
+            inner = conv((x2[:, :, i, None] * v).transpose(1, 2), s["k_long"], None, None, math.prod(s["factors"])).transpose(1, 2)
+            O += x1[:, :, i, None] * inner
+        return O.reshape(B, d, n).transpose(1, 2) @ s["W_out"].T + s["b_out"]
+    X = torch.fft.ifft(s["x"], norm="forward")      # the + sign, unscaled
+    return [torch.view_as_real(X.resolve_conj()), s["x"]]
+
+
 # Largest relative errors seen against the same computation in fp64, over the listed cases and 70 drawn ones: fp32 3.7e-7
 # (with the dense projections 1.0e-6); bf16 convolution 5.6e-3, gated-convolution layer 6.5e-3, transforms 4.5e-3, training
 # 3.7e-3, MLP 2.5e-3, M2 layer 2.4e-3; fp16 MLP 8.9e-4.  Each bound is two to five times that.
