@@ -15,7 +15,8 @@
 // convolution (a head's kernel spectrum is formed once per workgroup as for any batch), and one kernel forms the gated
 // sum over i in fp32.  For 16-bit tensors and nfft = 2048 = 64 x 32 the fused convolution kernel reads X2~[i] and V~[j]
 // through the head's index map and forms the products on its loads; otherwise one kernel writes them as a
-// (B d_h^2, d / d_h, n) tensor for the library's convolution.
+// (B d_h^2, d / d_h, n) tensor for the library's convolution.  Heads of 5 to 16 features go another way where that is
+// cheaper: csrc/hyena_heads.hip takes the sum over i first and needs no convolutions.
 #include <dlfcn.h>
 #include <mutex>
 
@@ -247,7 +248,12 @@ static int run(const void *u, const void *W_in, const void *b_in, const void *k_
         if (rc) return rc;
     }
     // 2. short depthwise convolutions (with the projection bias)
-    {
+    const bool paired = hyena_heads_supported(B, n, d, klen, nfft, dh);
+    if (paired) {   // and 3. for heads of few features: every pair of positions instead of d_h^2 convolutions
+        o = shrt;
+        int rc = launch_hyena_heads(proj, (char *)o + align_up(plane * es, 256), o, k_short, b_in, k_long, B, d, n, taps, klen, dh, dt, s);
+        if (rc) return rc;
+    } else {
         const int64_t rows = (int64_t)3 * B * d, total = rows * (n / 8);
         const int64_t blocks = (total + 255) / 256;
         hipLaunchKernelGGL(short_conv_kernel<T>, dim3((unsigned)(blocks > 65536 ? 65536 : blocks)), dim3(256), 0, s, proj, shrt,
@@ -255,7 +261,8 @@ static int run(const void *u, const void *W_in, const void *b_in, const void *k_
         MONARCH_HIP_CHECK(hipGetLastError());
     }
     // 3. O = X1~ o conv(k_long, X2~ o V~); with heads: outer products, d_h^2 convolutions per head, gated sum
-    if (dh > 1) {
+    if (paired) {   // done
+    } else if (dh > 1) {
         const int heads = d / dh;
         if (conv_mfma_2048_supported(n, klen, factors, nf, dt)) {
             // the fused 64 x 32 kernel reads V~[j] and X2~[i] through the head's index map: no tensor of outer products
@@ -297,6 +304,8 @@ static int run(const void *u, const void *W_in, const void *b_in, const void *k_
 size_t hyena_layer_workspace_bytes(int B, int n, int d, int klen, int nfft, const int *factors, int nf, int head_dim, monarch_dtype dt)
 {
     const size_t es = dtype_size(dt), plane = (size_t)B * d * n * es;
+    if (hyena_heads_supported(B, n, d, klen, nfft, head_dim))
+        return align_up(3 * plane, 256) + align_up(plane, 256) + align_up(hyena_heads_bytes(B, n, d, head_dim, dt), 256);
     const size_t outer = head_dim > 1 ? 2 * align_up((size_t)head_dim * plane, 256) : 0;
     const int conv_B = B * head_dim * head_dim, conv_H = d / head_dim;
     return 2 * align_up(3 * plane, 256) + align_up(plane, 256) + outer +

@@ -122,3 +122,17 @@ def test_heads_argument_checks(mm):
                      device="cuda")
     with pytest.raises((RuntimeError, ValueError)):
         mm.monarch_hyena_heads_layer(*t, (8, 16), 4, ws=ws)                # workspace too small
+
+
+# the pairs kernel: steps of 32 and units of 64 positions with remainders, one position piece, kernels shorter than a unit,
+# every padding of the features (5 .. 16), batches that leave waves of a workgroup idle; fp32 and bf16
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("B,n,d,dh,klen,factors", [(1, 8, 16, 16, 8, (16, 16)), (3, 40, 45, 9, 40, (16, 16)), (5, 72, 10, 5, 7, (16, 16)),
+                                                   (2, 512, 36, 6, 512, (64, 32)), (1, 1032, 48, 16, 1, (64, 64)),
+                                                   (2, 1032, 24, 12, 1000, (64, 64)), (1, 2048, 32, 8, 2048, (64, 64))])
+def test_heads_pairs(mm, B, n, d, dh, klen, factors, bf16):
+    announce("hyena layer heads by pairs", B, n, d, dh, klen, factors, bf16)
+    w = workloads.hyena_layer_inputs(B, n, d, ks=3, klen=klen, seed=n + d + dh, bf16=bf16, head_dim=dh)
+    nfft = int(np.prod(factors))
+    # fp32 as the layer above; bf16: projections, short convolutions, k S and both results rounded once each
+    assert rel_l2(_run_heads(mm, w, factors, dh, bf16), _want_heads(w, nfft, dh)) <= (2 * TOL_BF16 if bf16 else 5 * TOL_F32)
