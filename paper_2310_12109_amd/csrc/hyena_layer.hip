@@ -248,7 +248,10 @@ static int run(const void *u, const void *W_in, const void *b_in, const void *k_
         if (rc) return rc;
     }
     // 2. short depthwise convolutions (with the projection bias)
-    const bool paired = hyena_heads_supported(B, n, d, klen, nfft, dh);
+    // (the scratch of the calls without it is more than enough but for rows of a few positions of small heads)
+    const size_t heads_ws = align_up(3 * plane * es, 256) + align_up(plane * es, 256) + hyena_heads_bytes(B, n, d, dh, dt);
+    const bool paired = hyena_heads_supported(B, n, d, klen, nfft, dh) &&
+                        heads_ws <= hyena_layer_workspace_bytes(B, n, d, klen, nfft, factors, nf, dh, dt);
     if (paired) {   // and 3. for heads of few features: every pair of positions instead of d_h^2 convolutions
         o = shrt;
         int rc = launch_hyena_heads(proj, (char *)o + align_up(plane * es, 256), o, k_short, b_in, k_long, B, d, n, taps, klen, dh, dt, s);
@@ -304,8 +307,6 @@ static int run(const void *u, const void *W_in, const void *b_in, const void *k_
 size_t hyena_layer_workspace_bytes(int B, int n, int d, int klen, int nfft, const int *factors, int nf, int head_dim, monarch_dtype dt)
 {
     const size_t es = dtype_size(dt), plane = (size_t)B * d * n * es;
-    if (hyena_heads_supported(B, n, d, klen, nfft, head_dim))
-        return align_up(3 * plane, 256) + align_up(plane, 256) + align_up(hyena_heads_bytes(B, n, d, head_dim, dt), 256);
     const size_t outer = head_dim > 1 ? 2 * align_up((size_t)head_dim * plane, 256) : 0;
     const int conv_B = B * head_dim * head_dim, conv_H = d / head_dim;
     return 2 * align_up(3 * plane, 256) + align_up(plane, 256) + outer +
