@@ -260,3 +260,30 @@ def test_config5a_order3_sampled_rows(mm, bf16):
     # B=1, H=256, n=131072 padded to 262144 = 64^3: the oracle's direct sum on 2 seeded rows.
     announce("conv c5a sampled", "bf16" if bf16 else "fp32")
     _sampled_rows_check(mm, "c5a_conv", bf16, 2, TOL_BF16 if bf16 else TOL_F32)
+
+
+# the fp32 kernel that holds a pair of rows in registers: every length it takes, one and several channels per workgroup with
+# a remainder, odd n and klen, odd batches, n past half the transform, every gate combination, a two-sided kernel
+@pytest.mark.parametrize("B,H,n,klen,factors,gates,causal", [
+    (1, 1, 1, 1, (16, 16), "normal", True),
+    (5, 17, 127, 128, (16, 16), "normal", False),
+    (2, 9, 255, 2, (16, 16), "none", True),
+    (3, 9, 251, 250, (32, 16), "normal", True),
+    (4, 5, 509, 512, (8, 64), "in", False),
+    (7, 5, 511, 511, (32, 32), "out", True),
+    (2, 3, 1024, 1023, (64, 32), "normal", True),
+    (3, 2, 1500, 549, (64, 32), "in", True),
+    (5, 3, 2004, 2004, (64, 64), "normal", True),
+    (2, 2, 4001, 96, (16, 16, 16), "out", True),
+    (3, 2, 4096, 4096, (128, 64), "normal", True),
+    (2, 2, 4097, 8192, (64, 128), "none", False),
+])
+def test_fp32_rows_in_registers(mm, B, H, n, klen, factors, gates, causal):
+    announce("conv fp32 rows in registers", B, H, n, klen, factors, gates, causal)
+    nfft = int(np.prod(factors))
+    w = workloads.conv_inputs(B, H, n, seed=n + klen, gates="none" if gates == "none" else "normal")
+    w["k"] = np.random.default_rng(klen).standard_normal((H, klen)).astype(np.float32)
+    if gates in ("in", "out"):
+        w["g_out" if gates == "in" else "g_in"] = None
+    # a transform of radix 2..32 steps in fp32: error about 2^-24 sqrt(log2 N), far below the bound of the fp32 paths
+    assert rel_l2(_run(mm, w, factors, False, causal), _oracle(w, nfft, causal)) <= TOL_F32
