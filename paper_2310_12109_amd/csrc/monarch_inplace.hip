@@ -9,10 +9,14 @@
 //   R: block k contracts c (stride SH)  ->  (r, k);     L: block r contracts k (stride 1)  ->  (r, s) = y[s b + r]
 // so the three permutations of M = P L P R P cost nothing and the product ends transposed in the tile.  The mixer's
 // second matrix takes that layout as it is (R2: block k' = s contracts c' = r with stride 1, L2: block r' contracts
-// k' with stride SH) and ends in natural order.  Rows sit on the MFMA column index.  The factors (b^3 floats each) stay
-// in L2: a block's matrix is read as the A operand, 16 bytes per lane (lane (row, group g) takes columns
-// (b/4) g .. of its row, the contraction index of MFMA j being (b/4) g + j), the next row tile's weights requested
-// while the current one is multiplied.
+// k' with stride SH) and ends in natural order.  Rows sit on the MFMA column index.  The factors (b^3 elements each) stay
+// in L2 and are read as the A operand, 16 bytes per lane, a ring of requests ahead of the products.  bf16 factors meet the
+// fp32 values of the tile on the bf16 instruction, the values split into three bf16 parts: 16384 rows of b = 32 through the
+// mixer (the two halves of an M2 layer of 16 x 1024 x 1024) 77 and 90 us -> 45 and 50 us with the ring, the pitches, one
+// index division per tile instead of one per piece and, for transposed rows, neighbouring tiles on one XCD (277 -> 103 MB
+// past L2).  What is left: vector instructions (18 and 26 us, half of them the splitting), LDS (11 us), memory (13 us).
+// fp32 (12288 rows, both gates): 89 -> 83 us, all workgroups loading, multiplying and storing at the same time.
+#include "half16.h"
 #include "kernels.h"
 
 namespace monarch {
@@ -54,64 +58,158 @@ __device__ __forceinline__ void st4s(bf16_t *p, f32x4 v)
     store_stream8(p, *reinterpret_cast<const uint2 *>(h));
 }
 
-// b = 32: tiles of 16 rows (74 KB: two workgroups of 8 waves per compute unit); b = 64: tiles of 8 rows (139 KB, one
-// workgroup of 16 waves; columns 8..15 of the MFMA repeat the rows).  SH = b + 4: four lane groups that read rows
-// (b/4) g of a column are 16 banks apart; the row pitch is 1 (mod 64).
+// b = 32: tiles of 16 rows (78 KB: two workgroups of 8 waves per compute unit); b = 64: tiles of 8 rows (133 KB, one
+// workgroup of 16 waves; columns 8..15 of the MFMA repeat the rows).  The pitches SH (of the high digit) and ROWP (of a row)
+// have the fewest LDS passes of all pairs up to SH = b + 8 over the accesses below, 64 banks: per tile of the mixer 5632
+// at b = 32 (8192 with 36, 1153), 10240 at b = 64 (20480 with 68, 4353).
 template <int BS>
 struct Geo {
-    static constexpr int N = BS * BS, SH = BS + 4, TV = BS == 32 ? 16 : 8, ROWP = BS * SH + 1;
+    static constexpr int N = BS * BS, SH = BS == 32 ? 38 : 65, TV = BS == 32 ? 16 : 8, ROWP = BS == 32 ? 1225 : 4169;
     static constexpr int THREADS = BS == 32 ? 512 : 1024, WAVES = THREADS / 64, NBW = BS / WAVES;
     static constexpr int Q = BS / 4, RT = BS / 16;   // contraction indices per lane group; row tiles of a block
     static constexpr size_t LDS_BYTES = sizeof(float) * TV * ROWP;
 };
 
-// One factor in place.  Block blk contracts the digit that has stride SK; its other digit puts it at at(blk).
-// TRANS: the transposed blocks (lane (row i, group g) takes W[blk][(b/4) g + j][i]: a column of the block, 4-byte
-// loads that run along i across the 16 lanes of a group).
-template <typename T, int BS, int SK, bool TRANS = false, typename At>
-__device__ __forceinline__ void stage(float *tile, const T *__restrict__ W, int wave, int lane, At at)
+// The blocks' matrices on their way from L2: a wave's items of a stage are (block, row tile) pairs; DEPTH of them (32
+// registers) are requested ahead, the first ones of a stage before the barrier in front of it.  One item ahead, every
+// stage began and went on by waiting for L2.
+//   fp32 (and transposed blocks): 16x16x4 MFMAs, lane (row i, group g) holds columns (b/4) g .. of its row
+//   bf16: 16x16x32 MFMAs, lane (row i, group g) holds columns 32 c + 8 g .. of its row for every c < b / 32
+template <typename T, bool TRANS> constexpr bool kHalf = sizeof(T) == 2 && !TRANS;
+template <typename T, int BS, bool TRANS = false>
+struct Ring {
+    static constexpr bool HALF = kHalf<T, TRANS>;
+    static constexpr int WV = HALF ? BS / 32 : BS / 16, DEPTH = HALF && BS == 64 ? 2 : 8 / WV, ITEMS = Geo<BS>::NBW * Geo<BS>::RT;
+    f32x4 w[DEPTH][WV];
+};
+
+template <typename T, int BS, bool TRANS>
+__device__ __forceinline__ void request(const T *__restrict__ src, int item, int wave, int lane, f32x4 (&dst)[Ring<T, BS, TRANS>::WV])
 {
     typedef Geo<BS> G;
+    constexpr int WV = Ring<T, BS, TRANS>::WV;
+    const int l16 = lane & 15, kg = lane >> 4;
+    // (a uniform address per item and one lane offset for all items and matrices: no address registers to keep)
+    const T *at = src + ((size_t)(wave * G::NBW + item / G::RT) * BS + (TRANS ? 0 : 16 * (item % G::RT))) * BS + (TRANS ? 16 * (item % G::RT) : 0);
+    if constexpr (TRANS) {   // lane (row i, group g) takes W[blk][(b/4) g + j][i]: loads run along i across a group's lanes
+        const uint32_t off = G::Q * kg * BS + l16;
+#pragma unroll
+        for (int p = 0; p < WV; ++p)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dst[p][e] = ld1(at + (4 * p + e) * BS + off);
+    } else if constexpr (sizeof(T) == 2) {
+        const uint32_t off = l16 * BS + 8 * kg;
+#pragma unroll
+        for (int p = 0; p < WV; ++p) dst[p] = *reinterpret_cast<const f32x4 *>(at + 32 * p + off);
+    } else {
+        const uint32_t off = l16 * BS + G::Q * kg;
+#pragma unroll
+        for (int p = 0; p < WV; ++p) dst[p] = ld4(at + 4 * p + off);
+    }
+}
+
+template <typename T, int BS, bool TRANS>
+__device__ __forceinline__ void preload(Ring<T, BS, TRANS> &ring, const T *__restrict__ W, int wave, int lane)
+{
+    typedef Ring<T, BS, TRANS> Rg;
+    asm volatile("" : "+s"(W));   // (the addresses are formed here, not kept over a persistent workgroup's tiles)
+#pragma unroll
+    for (int d = 0; d < Rg::DEPTH && d < Rg::ITEMS; ++d) request<T, BS, TRANS>(W, d, wave, lane, ring.w[d]);
+}
+
+// Eight fp32 values as three bf16 operands, x = hi + mid + lo exactly (8 + 8 + 8 significant bits; each part is the
+// remainder of the one before cut to its upper 16 bits).  Infinities and NaN are their own high parts.
+__device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+__device__ __forceinline__ void split3(const float (&x)[8], h16::op8 (&p)[3])
+{
+    uint32_t hi[8], mid[8], lo[8], top = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t v = __float_as_uint(x[j]);
+        top = top > (v & 0x7fffffffu) ? top : (v & 0x7fffffffu);
+        hi[j] = v;
+        const float r = x[j] - __uint_as_float(v & 0xffff0000u);
+        mid[j] = __float_as_uint(r);
+        lo[j] = __float_as_uint(r - __uint_as_float(mid[j] & 0xffff0000u));
+    }
+    if (__builtin_expect(top >= 0x7f800000u, 0)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if ((hi[j] & 0x7fffffffu) >= 0x7f800000u) {
+                if ((hi[j] & 0x7fffffffu) > 0x7f800000u) hi[j] |= 0x00400000u;   // (a NaN stays one without its low half)
+                mid[j] = lo[j] = 0;
+            }
+    }
+    p[0] = h16::op8{high_halves(hi[0], hi[1]), high_halves(hi[2], hi[3]), high_halves(hi[4], hi[5]), high_halves(hi[6], hi[7])};
+    p[1] = h16::op8{high_halves(mid[0], mid[1]), high_halves(mid[2], mid[3]), high_halves(mid[4], mid[5]), high_halves(mid[6], mid[7])};
+    p[2] = h16::op8{high_halves(lo[0], lo[1]), high_halves(lo[2], lo[3]), high_halves(lo[4], lo[5]), high_halves(lo[6], lo[7])};
+}
+
+// One factor in place, its first items in the ring.  Block blk contracts the digit that has stride SK; its other digit
+// puts it at at(blk).  bf16 blocks meet the fp32 values of the tile as three bf16 operands (exact, so the products are
+// those of the fp32 instruction) on the 16x16x32 MFMA: 96 cycles per block of 32 instead of 512.  EXACT: the tile holds
+// bf16 values (the rows as loaded), one operand is enough.
+template <typename T, int BS, int SK, bool TRANS, bool EXACT, typename At>
+__device__ __forceinline__ void stage_from(Ring<T, BS, TRANS> &ring, float *tile, const T *__restrict__ W, int wave, int lane, At at)
+{
+    typedef Geo<BS> G;
+    typedef Ring<T, BS, TRANS> Rg;
     const int l16 = lane & 15, kg = lane >> 4;
     float *mine = tile + (l16 & (G::TV - 1)) * G::ROWP;
-    constexpr int ITEMS = G::NBW * G::RT, WV = G::Q / 4;   // (block, row tile) pairs of this wave; 16-byte pieces per lane
-    f32x4 w[2][WV];
     float anchor = 0.0f;
     // (the pointer passes through an empty asm that names the latest result, so that the compiler keeps each
     // request where it is written instead of hoisting all of a stage's loads to its top)
-    auto request = [&](int item, f32x4 (&dst)[WV]) {
-        const T *src = W;
-        asm volatile("" : "+s"(src) : "v"(anchor));
-        const int blk = wave * G::NBW + item / G::RT, rt = item % G::RT;
-        if constexpr (TRANS) {
-            const T *col = src + ((size_t)blk * BS + G::Q * kg) * BS + 16 * rt + l16;
-#pragma unroll
-            for (int p = 0; p < WV; ++p)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) dst[p][e] = ld1(col + (size_t)(4 * p + e) * BS);
-        } else {
-            const T *row = src + ((size_t)blk * BS + 16 * rt + l16) * BS + G::Q * kg;
-#pragma unroll
-            for (int p = 0; p < WV; ++p) dst[p] = ld4(row + 4 * p);
+    auto next = [&](int item) {
+        if (item + Rg::DEPTH < Rg::ITEMS) {
+            const T *src = W;
+            asm volatile("" : "+s"(src) : "v"(anchor));
+            request<T, BS, TRANS>(src, item + Rg::DEPTH, wave, lane, ring.w[item % Rg::DEPTH]);
         }
     };
-    request(0, w[0]);
 #pragma unroll
     for (int u = 0; u < G::NBW; ++u) {
         float *e = mine + at(wave * G::NBW + u);
-        float bv[G::Q];
-#pragma unroll
-        for (int j = 0; j < G::Q; ++j) bv[j] = e[(G::Q * kg + j) * SK];
         f32x4 acc[G::RT];
+        if constexpr (Rg::HALF) {
+            constexpr int CH = BS / 32, PARTS = EXACT ? 1 : 3;
+            h16::op8 b[CH][3];
 #pragma unroll
-        for (int rt = 0; rt < G::RT; ++rt) {
-            const int item = u * G::RT + rt;
-            if (item + 1 < ITEMS) request(item + 1, w[(item + 1) & 1]);
-            f32x4 a = {0, 0, 0, 0};
+            for (int c = 0; c < CH; ++c) {
+                float x[8];
 #pragma unroll
-            for (int j = 0; j < G::Q; ++j) a = mfma(w[item & 1][j >> 2][j & 3], bv[j], a);
-            acc[rt] = a;
-            anchor = a[0];
+                for (int j = 0; j < 8; ++j) x[j] = e[(32 * c + 8 * kg + j) * SK];
+                if constexpr (EXACT) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) b[c][0][j] = high_halves(__float_as_uint(x[2 * j]), __float_as_uint(x[2 * j + 1]));
+                } else split3(x, b[c]);
+            }
+#pragma unroll
+            for (int rt = 0; rt < G::RT; ++rt) {
+                const int item = u * G::RT + rt;
+                f32x4 a = {0, 0, 0, 0};
+#pragma unroll
+                for (int part = PARTS - 1; part >= 0; --part)
+#pragma unroll
+                    for (int c = 0; c < CH; ++c)
+                        a = h16::mfma<bf16_t>(__builtin_bit_cast(h16::op8, ring.w[item % Rg::DEPTH][c]), b[c][part], a);
+                acc[rt] = a;
+                anchor = a[0];
+                next(item);
+            }
+        } else {
+            float bv[G::Q];
+#pragma unroll
+            for (int j = 0; j < G::Q; ++j) bv[j] = e[(G::Q * kg + j) * SK];
+#pragma unroll
+            for (int rt = 0; rt < G::RT; ++rt) {
+                const int item = u * G::RT + rt;
+                f32x4 a = {0, 0, 0, 0};
+#pragma unroll
+                for (int j = 0; j < G::Q; ++j) a = mfma(ring.w[item % Rg::DEPTH][j >> 2][j & 3], bv[j], a);
+                acc[rt] = a;
+                anchor = a[0];
+                next(item);
+            }
         }
         // every input of the block has been read: the results take their places
         if (l16 < G::TV) {
@@ -123,16 +221,40 @@ __device__ __forceinline__ void stage(float *tile, const T *__restrict__ W, int 
     }
 }
 
+template <typename T, int BS, int SK, bool TRANS = false, typename At>
+__device__ __forceinline__ void stage(float *tile, const T *__restrict__ W, int wave, int lane, At at)
+{
+    Ring<T, BS, TRANS> ring;
+    preload<T, BS, TRANS>(ring, W, wave, lane);
+    stage_from<T, BS, SK, TRANS, false>(ring, tile, W, wave, lane, at);
+}
+
+// Tiles are handed out so that neighbouring ones run on one XCD at one time (workgroups go to the eight XCDs in turn):
+// tiles of transposed rows share cache lines.  An XCD takes a run of tiles, its workgroups in turn.
+struct Tiles {
+    int64_t first, end, step;
+    __device__ Tiles(int64_t ntiles)
+    {
+        // workgroups of the XCDs before x, of x: the tiles are divided alike
+        const int g = gridDim.x, x = blockIdx.x & 7, before = x * (g / 8) + (x < g % 8 ? x : g % 8);
+        step = g / 8 + (x < g % 8 ? 1 : 0);
+        first = ntiles * before / g + (blockIdx.x >> 3);
+        end = ntiles * (before + step) / g;
+    }
+};
+
 template <typename T, int BS>
-__global__ __launch_bounds__(Geo<BS>::THREADS, BS == 32 ? 2 : 1) void matmul_kernel(const T *__restrict__ x, const T *__restrict__ R,
+__global__ __launch_bounds__(Geo<BS>::THREADS, 4) void matmul_kernel(const T *__restrict__ x, const T *__restrict__ R,
                                                                                   const T *__restrict__ L, T *__restrict__ y, int64_t batch)
 {
     typedef Geo<BS> G;
     extern __shared__ __attribute__((aligned(16))) float tile[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t ntiles = (batch + G::TV - 1) / G::TV;
+    Ring<T, BS> ring;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int64_t v0 = t * G::TV;
+        preload<T, BS, false>(ring, R, wave, lane);
         for (int piece = threadIdx.x; piece < G::TV * G::N / 4; piece += G::THREADS) {
             const int v = piece / (G::N / 4), i = 4 * (piece % (G::N / 4));
             int64_t r = v0 + v;
@@ -142,9 +264,10 @@ __global__ __launch_bounds__(Geo<BS>::THREADS, BS == 32 ? 2 : 1) void matmul_ker
             d[0] = val[0]; d[1] = val[1]; d[2] = val[2]; d[3] = val[3];
         }
         __syncthreads();
-        stage<T, BS, G::SH>(tile, R, wave, lane, [](int k) { return k; });
+        stage_from<T, BS, G::SH, false, true>(ring, tile, R, wave, lane, [](int k) { return k; });
+        preload<T, BS, false>(ring, L, wave, lane);
         __syncthreads();
-        stage<T, BS, 1>(tile, L, wave, lane, [](int r) { return r * G::SH; });
+        stage_from<T, BS, 1, false, false>(ring, tile, L, wave, lane, [](int r) { return r * G::SH; });
         __syncthreads();
         // y[s b + r] sits at (r, s): a thread stores r = 4 q .. 4 q + 3 of one s
         for (int piece = threadIdx.x; piece < G::TV * G::N / 4; piece += G::THREADS) {
@@ -159,8 +282,8 @@ __global__ __launch_bounds__(Geo<BS>::THREADS, BS == 32 ? 2 : 1) void matmul_ker
 // opt: the options of the basic M2 layer (Sec. 3.2): an activation after the kernel product, rows that run along the
 // middle index of a (B, N, H) tensor (transposed: a tile's TV rows are TV neighbouring h of one batch entry, moved in
 // pieces of four rows of one position), and the skip connection and layer norm over the row at the store.
-template <typename T, int BS, bool GIN, bool GOUT>
-__global__ __launch_bounds__(Geo<BS>::THREADS, BS == 32 ? 2 : 1) void mixer_kernel(
+template <typename T, int BS, bool GIN, bool GOUT, bool TRANSPOSED>
+__global__ __launch_bounds__(Geo<BS>::THREADS, 4) void mixer_kernel(
     const T *__restrict__ u, const T *__restrict__ K, const T *__restrict__ g_in, const T *__restrict__ g_out,
     const T *__restrict__ R1, const T *__restrict__ L1, const T *__restrict__ R2, const T *__restrict__ L2, T *__restrict__ y,
     int64_t rows, int H, const MixOpt opt)
@@ -169,73 +292,78 @@ __global__ __launch_bounds__(Geo<BS>::THREADS, BS == 32 ? 2 : 1) void mixer_kern
     extern __shared__ __attribute__((aligned(16))) float tile[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t ntiles = (rows + G::TV - 1) / G::TV;
-    constexpr int PIECES = G::TV * G::N / 4;
-    // piece p of a tile: four elements and where they sit.  Plain rows: elements i .. i + 3 of row v; transposed: element i
-    // of rows v .. v + 3 (neighbouring h of one batch entry: contiguous in memory).
-    auto where = [&](int p, int64_t v0, int &v, int &i) -> int64_t {
-        if (opt.transposed) {
-            i = p / (G::TV / 4);
-            v = 4 * (p % (G::TV / 4));
-            // (rows is a multiple of TV here and a tile stays inside one batch entry: v0 = bt H + h0)
-            const int64_t bt = v0 / H, h0 = v0 - bt * H;
-            return (bt * G::N + i) * H + h0 + v;
-        }
-        v = p / (G::N / 4);
-        i = 4 * (p % (G::N / 4));
-        int64_t r = v0 + v;
-        if (r >= rows) r = rows - 1;   // (rows past the end: computed, never stored)
-        return r * G::N + i;
-    };
-    // the four tile words of a piece: natural position (hi, lo) = (i / b, i % b)
-    auto put = [&](int v, int i, f32x4 val) {
-        if (opt.transposed) {
-            float *d = tile + v * G::ROWP + (i / BS) * G::SH + i % BS;
-            d[0] = val[0]; d[G::ROWP] = val[1]; d[2 * G::ROWP] = val[2]; d[3 * G::ROWP] = val[3];
-        } else {
-            float *d = tile + v * G::ROWP + (i / BS) * G::SH + i % BS;
-            d[0] = val[0]; d[1] = val[1]; d[2] = val[2]; d[3] = val[3];
-        }
-    };
-    auto get = [&](int v, int i) -> f32x4 {
-        const float *d = tile + v * G::ROWP + (i / BS) * G::SH + i % BS;
-        if (opt.transposed) return f32x4{d[0], d[G::ROWP], d[2 * G::ROWP], d[3 * G::ROWP]};
-        return f32x4{d[0], d[1], d[2], d[3]};
-    };
-    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    constexpr int PIECES = G::TV * G::N / 4, PIECES_AHEAD = sizeof(T) == 2 ? 4 : 2;
+    Ring<T, BS> ring;
+    const Tiles mine(ntiles);
+    for (int64_t t = mine.first; t < mine.end; t += mine.step) {
         const int64_t v0 = t * G::TV;
+        const int64_t bt = v0 / H;           // (one division per tile, not one per piece)
+        const int h0 = (int)(v0 - bt * H);
+        // piece p of a tile: four elements and where they sit.  Plain rows: elements i .. i + 3 of row v; transposed: element i
+        // of rows v .. v + 3 (neighbouring h of one batch entry: contiguous in memory).
+        auto where = [&](int p, int &v, int &i) -> int64_t {
+            if (TRANSPOSED) {
+                i = p / (G::TV / 4);
+                v = 4 * (p % (G::TV / 4));
+                // (rows is a multiple of TV here and a tile stays inside one batch entry: v0 = bt H + h0)
+                return (bt * G::N + i) * H + h0 + v;
+            }
+            v = p / (G::N / 4);
+            i = 4 * (p % (G::N / 4));
+            int64_t r = v0 + v;
+            if (r >= rows) r = rows - 1;   // (rows past the end: computed, never stored)
+            return r * G::N + i;
+        };
+        // the four tile words of a piece: natural position (hi, lo) = (i / b, i % b)
+        constexpr int STEP = TRANSPOSED ? G::ROWP : 1;
+        auto put = [&](int v, int i, f32x4 val) {
+            float *d = tile + v * G::ROWP + (i / BS) * G::SH + i % BS;
+            d[0] = val[0]; d[STEP] = val[1]; d[2 * STEP] = val[2]; d[3 * STEP] = val[3];
+        };
+        auto get = [&](int v, int i) -> f32x4 {
+            const float *d = tile + v * G::ROWP + (i / BS) * G::SH + i % BS;
+            return f32x4{d[0], d[STEP], d[2 * STEP], d[3 * STEP]};
+        };
+        preload<T, BS, false>(ring, R1, wave, lane);
+#pragma unroll(PIECES_AHEAD)
         for (int piece = threadIdx.x; piece < PIECES; piece += G::THREADS) {
             int v, i;
-            const int64_t at = where(piece, v0, v, i);
+            const int64_t at = where(piece, v, i);
             f32x4 val = ld4(u + at);
             if (GIN) val *= ld4(g_in + at);
             put(v, i, val);
         }
         __syncthreads();
-        stage<T, BS, G::SH>(tile, R1, wave, lane, [](int k) { return k; });
+        stage_from<T, BS, G::SH, false, !GIN>(ring, tile, R1, wave, lane, [](int k) { return k; });
+        preload<T, BS, false>(ring, L1, wave, lane);
         __syncthreads();
-        stage<T, BS, 1>(tile, L1, wave, lane, [](int r) { return r * G::SH; });
+        stage_from<T, BS, 1, false, false>(ring, tile, L1, wave, lane, [](int r) { return r * G::SH; });
+        preload<T, BS, false>(ring, R2, wave, lane);
         __syncthreads();
         // kernel product: entry m = s b + r of the transform domain sits at (r, s)
+#pragma unroll(PIECES_AHEAD)
         for (int piece = threadIdx.x; piece < PIECES; piece += G::THREADS) {
             const int v = piece / (G::N / 4), m = 4 * (piece % (G::N / 4));
-            int64_t r = v0 + v;
-            if (r >= rows) r = rows - 1;
-            const f32x4 kv = ld4(K + (r % H) * G::N + m);
+            int h = h0 + v;   // of row v0 + v
+            if (h >= H) h = H >= G::TV ? h - H : h % H;
+            const f32x4 kv = ld4(K + (int64_t)h * G::N + m);
             float *sp = tile + v * G::ROWP + (m % BS) * G::SH + m / BS;
             f32x4 p = {sp[0] * kv[0], sp[G::SH] * kv[1], sp[2 * G::SH] * kv[2], sp[3 * G::SH] * kv[3]};
             if (opt.act) p = f32x4{fmaxf(p[0], 0.0f), fmaxf(p[1], 0.0f), fmaxf(p[2], 0.0f), fmaxf(p[3], 0.0f)};
             sp[0] = p[0]; sp[G::SH] = p[1]; sp[2 * G::SH] = p[2]; sp[3 * G::SH] = p[3];
         }
         __syncthreads();
-        stage<T, BS, 1>(tile, R2, wave, lane, [](int k) { return k * G::SH; });
+        stage_from<T, BS, 1, false, false>(ring, tile, R2, wave, lane, [](int k) { return k * G::SH; });
+        preload<T, BS, false>(ring, L2, wave, lane);
         __syncthreads();
-        stage<T, BS, G::SH>(tile, L2, wave, lane, [](int r) { return r; });
+        stage_from<T, BS, G::SH, false, false>(ring, tile, L2, wave, lane, [](int r) { return r; });
         __syncthreads();
         if (opt.layer_norm) {
             // result (gated) + u back into the tile, then a wave per row: mean, variance, scale and shift
+#pragma unroll(PIECES_AHEAD)
             for (int piece = threadIdx.x; piece < PIECES; piece += G::THREADS) {
                 int v, i;
-                const int64_t at = where(piece, v0, v, i);
+                const int64_t at = where(piece, v, i);
                 f32x4 val = get(v, i);
                 if (GOUT) val *= ld4(g_out + at);
                 put(v, i, val + ld4(u + at));
@@ -243,29 +371,45 @@ __global__ __launch_bounds__(Geo<BS>::THREADS, BS == 32 ? 2 : 1) void mixer_kern
             __syncthreads();
             for (int v = wave; v < G::TV; v += G::WAVES) {
                 const float *row = tile + v * G::ROWP;
+                auto four = [&](int q) -> f32x4 {   // four neighbouring elements of the row
+                    const float *d = row + ((256 * q + 4 * lane) / BS) * G::SH + (4 * lane) % BS;
+                    return f32x4{d[0], d[1], d[2], d[3]};
+                };
                 float sum = 0.0f;
-                for (int j = lane; j < G::N; j += 64) sum += row[(j / BS) * G::SH + j % BS];
+#pragma unroll 4
+                for (int q = 0; q < G::N / 256; ++q) {
+                    const f32x4 x = four(q);
+                    sum += (x[0] + x[1]) + (x[2] + x[3]);
+                }
                 for (int m = 32; m; m >>= 1) sum += __shfl_xor(sum, m);
                 const float mean = sum / G::N;
                 float sq = 0.0f;
-                for (int j = lane; j < G::N; j += 64) {
-                    const float dlt = row[(j / BS) * G::SH + j % BS] - mean;
-                    sq += dlt * dlt;
+#pragma unroll 4
+                for (int q = 0; q < G::N / 256; ++q) {
+                    const f32x4 x = four(q) - mean;
+                    sq += (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
                 }
                 for (int m = 32; m; m >>= 1) sq += __shfl_xor(sq, m);
                 const float rstd = rsqrtf(sq / G::N + opt.eps);
                 const int64_t r = v0 + v;
-                if (r < rows)
-                    for (int j = lane; j < G::N; j += 64) {
-                        const int64_t at = opt.transposed ? ((v0 / H) * G::N + j) * H + v0 % H + v : r * G::N + j;
-                        y[at] = from_f32<T>((row[(j / BS) * G::SH + j % BS] - mean) * rstd * to_f32(((const T *)opt.gamma)[j]) +
-                                            to_f32(((const T *)opt.beta)[j]));
+                if (r < rows) {
+#pragma unroll 4
+                    for (int q = 0; q < G::N / 256; ++q) {
+                        const int j = 256 * q + 4 * lane;
+                        const f32x4 gm = ld4((const T *)opt.gamma + j), bb = ld4((const T *)opt.beta + j);
+                        const f32x4 res = (four(q) - mean) * rstd * gm + bb;
+                        if (TRANSPOSED) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) y[(bt * G::N + j + e) * H + h0 + v] = from_f32<T>(res[e]);
+                        } else st4(y + r * G::N + j, res);
                     }
+                }
             }
         } else {
+#pragma unroll(PIECES_AHEAD)
             for (int piece = threadIdx.x; piece < PIECES; piece += G::THREADS) {
                 int v, i;
-                const int64_t at = where(piece, v0, v, i);
+                const int64_t at = where(piece, v, i);
                 if (v0 + v < rows) {
                     f32x4 val = get(v, i);
                     if (GOUT) val *= ld4(g_out + at);
@@ -780,7 +924,7 @@ static int launch_mixer_g(const void *u, const void *K, const void *g_in, const 
     typedef Geo<BS> G;
     int64_t grid = 0;
     if (int rc = grid_for<BS>((rows + G::TV - 1) / G::TV, &grid)) return rc;
-    auto kern = mixer_kernel<T, BS, GIN, GOUT>;
+    auto kern = opt.transposed ? mixer_kernel<T, BS, GIN, GOUT, true> : mixer_kernel<T, BS, GIN, GOUT, false>;
     MONARCH_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS_BYTES));
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(G::THREADS), G::LDS_BYTES, s, (const T *)u, (const T *)K, (const T *)g_in,
                        (const T *)g_out, (const T *)R1, (const T *)L1, (const T *)R2, (const T *)L2, (T *)y, rows, H, opt);

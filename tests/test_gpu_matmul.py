@@ -127,3 +127,23 @@ def test_large_batch_sampled(mm):
     xs = x[torch.from_numpy(rows).cuda()].cpu().numpy()
     got = host(y[torch.from_numpy(rows).cuda()])
     assert rel_l2(got, oracle.matmul(xs, w["R"], w["L"])) <= TOL_F32
+
+
+# bf16 blocks of 32 and 64: the tile's fp32 values meet the bf16 matrices as three bf16 parts.  A whole and a partial tile,
+# magnitudes over sixty decades (the parts of a value lie up to 2^-24 below it), and one infinity and one NaN, which
+# must come out where plain floating point puts them and nowhere else
+@pytest.mark.parametrize("b,batch", [(32, 16), (32, 21), (64, 8), (64, 3)])
+def test_bf16_parts_of_wide_and_non_finite_values(mm, b, batch):
+    announce("matmul bf16 parts", b, batch)
+    g = torch.Generator().manual_seed(b + batch)
+    x = (torch.randn(batch, b * b, generator=g) * 10.0 ** torch.linspace(-30, 30, batch)[:, None]).bfloat16()
+    R, L = (torch.randn(b, b, b, generator=g).mul(b ** -0.5).bfloat16() for _ in range(2))
+    x[0, 5] = float("inf")
+    x[1, 7] = float("nan")
+    got = mm.monarch_matmul(x.cuda(), R.cuda(), L.cuda()).cpu().double()
+    z = torch.einsum("krc,xck->xrk", R.double(), x.double().reshape(batch, b, b))
+    want = torch.einsum("jlc,xjc->xlj", L.double(), z).reshape(batch, b * b)
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
+    assert torch.equal(got[torch.isinf(got)].sign(), want[torch.isinf(want)].sign())
+    for r in range(2, batch):   # the result's rounding to bf16 (2^-9) is the only one that shows
+        assert rel_l2(got[r].numpy(), want[r].numpy()) <= 2.0 ** -8
