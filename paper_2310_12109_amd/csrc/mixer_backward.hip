@@ -6,6 +6,7 @@
 //   dg_out = dy o w         dw = dy o g_out     (dt, dR2, dL2) = grad of M2 at (t, dw)
 //   dK[h] = sum_b dt o s    ds = dt o K         (da, dR1, dL1) = grad of M1 at (a, ds)
 //   du = da o g_in          dg_in = da o u
+// Blocks of 32 take two kernels instead (csrc/monarch_inplace), which keep everything but ds in LDS and registers.
 #include "kernels.h"
 
 namespace monarch {
@@ -100,6 +101,19 @@ __global__ void clear_kernel(float *p, size_t n)
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0.0f;
 }
 
+// the sums of a call, whole pieces of four floats each; any may be null
+struct SumBuffers {
+    float *p[5];
+    size_t n[5];
+};
+__global__ void clear_sums_kernel(SumBuffers b)
+{
+    const size_t stride = (size_t)gridDim.x * blockDim.x, first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int q = 0; q < 5; ++q)
+        if (b.p[q])
+            for (size_t i = first; i < b.n[q] / 4; i += stride) reinterpret_cast<f32x4 *>(b.p[q])[i] = f32x4{0, 0, 0, 0};
+}
+
 static unsigned blocks_for(size_t n)
 {
     const size_t b = (n + THREADS - 1) / THREADS;
@@ -187,6 +201,13 @@ int launch_mixer_backward(const void *u, const void *K, const void *g_in, const 
                           void *dg_out, float *dR1, float *dL1, float *dR2, float *dL2, int64_t B, int H, int bs,
                           monarch_dtype dt, void *ws, hipStream_t s)
 {
+    if (mixer_backward_inplace_takes(B, bs, dt)) {
+        const size_t w = (size_t)bs * bs * bs;
+        const mixb::SumBuffers sums = {{dK, dR1, dL1, dR2, dL2}, {(size_t)H * bs * bs, w, w, w, w}};
+        if (dK || dR1 || dL1 || dR2 || dL2) hipLaunchKernelGGL(mixb::clear_sums_kernel, dim3(256), dim3(256), 0, s, sums);
+        MONARCH_HIP_CHECK(hipGetLastError());
+        return launch_mixer_backward_inplace(u, K, g_in, g_out, R1, L1, R2, L2, dy, ws, du, dK, dg_in, dg_out, dR1, dL1, dR2, dL2, B, H, dt, s);
+    }
     if (dt == MONARCH_F32)
         return mixb::run<float>(u, K, g_in, g_out, R1, L1, R2, L2, dy, du, dK, dg_in, dg_out, dR1, dL1, dR2, dL2, B, H, bs, dt, ws, s);
     return mixb::run<bf16_t>(u, K, g_in, g_out, R1, L1, R2, L2, dy, du, dK, dg_in, dg_out, dR1, dL1, dR2, dL2, B, H, bs, dt, ws, s);

@@ -426,10 +426,9 @@ __global__ __launch_bounds__(Geo<BS>::THREADS, 4) void mixer_kernel(
 //   dmid(r, k) = sum_s L[r][s][k] dy(r, s)    (block r of L transposed contracts s, stride 1)
 //   dx(c, k)   = sum_r R[k][r][c] dmid(r, k)  (block k of R transposed contracts r, stride SH)
 //   dL[r][s][k] = sum_v dy_v(r, s) mid_v(r, k),   dR[k][r][c] = sum_v dmid_v(r, k) x_v(c, k).
-// Two tiles of 16 rows (forward values and gradients, 148 KB): a factor's gradient is, per block and 16 x 16 piece
-// of it, four MFMAs whose contraction index is the row of the tile; the sums of a wave's four blocks (64 registers)
-// stay in registers over all tiles of the workgroup and are added to the caller's cleared buffer once.  Two
-// launches, because x is overwritten by mid and dy by dmid: one gives dx and dL, the other dR.
+// Two tiles of 16 rows (forward values and gradients, 157 KB, one workgroup per compute unit): a factor's gradient is, per
+// block and 16 x 16 piece of it, four MFMAs whose contraction index is the row of the tile; the sums of a wave's four
+// blocks (64 registers a factor) stay in registers over all tiles of the workgroup and are added to the cleared buffer once.
 
 // sum[u][it][jt] += (rows 16 it .. of side A)^T (rows 16 jt .. of side B) of block wave NBW + u, over the tile's rows
 template <int BS, int SK, typename At>
@@ -474,95 +473,327 @@ __device__ __forceinline__ void flush(float *dW, int wave, int lane, const f32x4
                     atomicAdd(dW + ((size_t)(wave * G::NBW + u) * BS + 16 * it + 4 * kg + r) * BS + 16 * jt + l16, sum[u][it][jt][r]);
 }
 
-// x -> fw tile at (c, k); dy -> gr tile at (r, s), zero for the rows past the batch (their x is a copy of the last row)
-template <typename T, int BS>
-__device__ __forceinline__ void load_pair(float *fw, float *gr, const T *x, const T *dy, int64_t v0, int64_t batch, bool want_x)
+// A transposed factor on its way from L2, by block: lane (i, group g) takes columns 2 i, 2 i + 1 of the block's rows 8 g ..
+// 8 g + 7, which serve both row tiles of the result (row tile rt holds outputs 2 i + rt): 8 loads of a pair where one per
+// row and row tile took 16.  DEPTH blocks are requested ahead.
+template <typename T> struct Pair;
+template <> struct Pair<float> { typedef float2 type; };
+template <> struct Pair<bf16_t> { typedef uint32_t type; };
+template <typename T>
+struct TRing {
+    static constexpr int DEPTH = 2;
+    typename Pair<T>::type w[DEPTH][8];
+};
+
+template <typename T>
+__device__ __forceinline__ void request_t(const T *__restrict__ src, int blk, int lane, typename Pair<T>::type (&dst)[8])
 {
-    typedef Geo<BS> G;
-    for (int piece = threadIdx.x; piece < G::TV * G::N / 4; piece += G::THREADS) {
-        const int v = piece / (G::N / 4), i = 4 * (piece % (G::N / 4));
-        const bool live = v0 + v < batch;
-        const int64_t r = live ? v0 + v : batch - 1;
-        if (want_x) {
-            const f32x4 val = ld4(x + r * G::N + i);
-            float *d = fw + v * G::ROWP + (i / BS) * G::SH + i % BS;
-            d[0] = val[0]; d[1] = val[1]; d[2] = val[2]; d[3] = val[3];
+    const T *at = src + (size_t)blk * 32 * 32;
+    const uint32_t off = 8 * (lane >> 4) * 32 + 2 * (lane & 15);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) dst[j] = *reinterpret_cast<const typename Pair<T>::type *>(at + 32 * j + off);
+}
+
+template <typename T>
+__device__ __forceinline__ void preload_t(TRing<T> &ring, const T *__restrict__ W, int wave, int lane)
+{
+    asm volatile("" : "+s"(W));
+#pragma unroll
+    for (int d = 0; d < TRing<T>::DEPTH; ++d) request_t<T>(W, wave * Geo<32>::NBW + d, lane, ring.w[d]);
+}
+
+// One transposed factor in place, its first blocks in the ring.
+template <typename T, int SK, typename At>
+__device__ __forceinline__ void stage_t(TRing<T> &ring, float *tile, const T *__restrict__ W, int wave, int lane, At at)
+{
+    typedef Geo<32> G;
+    constexpr int DEPTH = TRing<T>::DEPTH;
+    const int l16 = lane & 15, kg = lane >> 4;
+    float *mine = tile + l16 * G::ROWP;
+#pragma unroll
+    for (int u = 0; u < G::NBW; ++u) {
+        float *e = mine + at(wave * G::NBW + u);
+        const auto &w = ring.w[u % DEPTH];
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = e[(8 * kg + j) * SK];
+        f32x4 acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+        if constexpr (sizeof(T) == 2) {
+            h16::op8 b[3], a[2];
+            split3(x, b);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                a[0][j] = __builtin_amdgcn_perm(w[2 * j + 1], w[2 * j], 0x05040100u);
+                a[1][j] = __builtin_amdgcn_perm(w[2 * j + 1], w[2 * j], 0x07060302u);
+            }
+#pragma unroll
+            for (int part = 2; part >= 0; --part)
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) acc[rt] = h16::mfma<bf16_t>(a[rt], b[part], acc[rt]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                acc[0] = mfma(w[j].x, x[j], acc[0]);
+                acc[1] = mfma(w[j].y, x[j], acc[1]);
+            }
         }
-        f32x4 g = ld4(dy + r * G::N + i);
-        if (!live) g = f32x4{0, 0, 0, 0};
-        float *sp = gr + v * G::ROWP + (i % BS) * G::SH + i / BS;   // dy[s b + r] at (r, s): i / b = s, i % b = r .. r + 3
-        sp[0] = g[0]; sp[G::SH] = g[1]; sp[2 * G::SH] = g[2]; sp[3 * G::SH] = g[3];
+        if (u + DEPTH < G::NBW) {
+            const T *src = W;
+            asm volatile("" : "+s"(src) : "v"(acc[1][0]));   // (the request stays behind these products)
+            request_t<T>(src, wave * G::NBW + u + DEPTH, lane, ring.w[u % DEPTH]);
+        }
+        // every input of the block has been read: the results take their places
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) e[(8 * kg + 2 * r + rt) * SK] = acc[rt][r];
     }
 }
 
-template <typename T, int BS, bool DX, bool DL>
-__global__ __launch_bounds__(Geo<BS>::THREADS, 1) void backward_dx_dl_kernel(const T *__restrict__ x, const T *__restrict__ R,
-                                                                               const T *__restrict__ L, const T *__restrict__ dy,
-                                                                               T *__restrict__ dx, float *__restrict__ dL, int64_t batch)
+// The same value, unknown to the compiler: addresses derived from it are formed at their use instead of being kept in
+// registers over a persistent workgroup's tiles (with the sums there is no room for them: 556 bytes of spills a lane).
+__device__ __forceinline__ int fresh(int v)
 {
-    typedef Geo<BS> G;
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// A thread's share of a 16 x 1024 tile: piece p holds elements i .. i + 3 of row v(p).
+struct Share {
+    static constexpr int PIECES = Geo<32>::TV * Geo<32>::N / 4 / Geo<32>::THREADS;
+    const int v0, i;
+    explicit __device__ Share(int thread) : v0(thread >> 8), i(4 * (thread & 255)) {}
+    __device__ int v(int p) const { return v0 + 2 * p; }
+    __device__ int natural(int p) const { return v(p) * Geo<32>::ROWP + (i / 32) * Geo<32>::SH + i % 32; }   // elements 1 apart
+    __device__ int swapped(int p) const { return v(p) * Geo<32>::ROWP + (i % 32) * Geo<32>::SH + i / 32; }   // SH apart
+};
+template <int STEP> __device__ __forceinline__ void put(float *d, f32x4 v) { d[0] = v[0]; d[STEP] = v[1]; d[2 * STEP] = v[2]; d[3 * STEP] = v[3]; }
+template <int STEP> __device__ __forceinline__ f32x4 get(const float *d) { return f32x4{d[0], d[STEP], d[2 * STEP], d[3 * STEP]}; }
+
+typedef f32x4 Sums[Geo<32>::NBW][Geo<32>::RT][Geo<32>::RT];
+__device__ __forceinline__ void zero(Sums &sum)
+{
+    for (auto &u : sum)
+        for (auto &it : u)
+            for (auto &jt : it) jt = f32x4{0, 0, 0, 0};
+}
+
+// Gradients of y = M (g_in o u) (g_in null: of M u) for rows of 1024: dx, dg_in, dR and dL, each may be null.  The values
+// that dR needs again after mid took their places wait in registers.
+template <typename T>
+__global__ __launch_bounds__(512, 2) void backward_kernel(const T *__restrict__ u, const T *__restrict__ g_in, const T *__restrict__ R,
+                                                          const T *__restrict__ L, const T *__restrict__ dy, T *__restrict__ dx,
+                                                          T *__restrict__ dg_in, float *__restrict__ dR, float *__restrict__ dL, int64_t batch)
+{
+    typedef Geo<32> G;
     extern __shared__ __attribute__((aligned(16))) float tile[];
     float *fw = tile, *gr = tile + G::TV * G::ROWP;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    f32x4 sum[G::NBW][G::RT][G::RT];
-#pragma unroll
-    for (int u = 0; u < G::NBW; ++u)
-#pragma unroll
-        for (int it = 0; it < G::RT; ++it)
-#pragma unroll
-            for (int jt = 0; jt < G::RT; ++jt) sum[u][it][jt] = f32x4{0, 0, 0, 0};
+    const bool want_dx = dx || dg_in;
+    Sums sumR, sumL;
+    zero(sumR);
+    zero(sumL);
     const int64_t ntiles = (batch + G::TV - 1) / G::TV;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int64_t v0 = t * G::TV;
-        load_pair<T, BS>(fw, gr, x, dy, v0, batch, DL);
-        __syncthreads();
-        if constexpr (DL) {
-            stage<T, BS, G::SH>(fw, R, wave, lane, [](int k) { return k; });   // x -> mid
-            __syncthreads();
-            outer<BS, 1>(gr, fw, wave, lane, [](int r) { return r * G::SH; }, sum);   // dL[r][s][k]: dy(r, s) x mid(r, k)
-            __syncthreads();
-        }
-        if constexpr (DX) {
-            stage<T, BS, 1, true>(gr, L, wave, lane, [](int r) { return r * G::SH; });   // dy -> dmid
-            __syncthreads();
-            stage<T, BS, G::SH, true>(gr, R, wave, lane, [](int k) { return k; });       // dmid -> dx at (c, k)
-            __syncthreads();
-            for (int piece = threadIdx.x; piece < G::TV * G::N / 4; piece += G::THREADS) {
-                const int v = piece / (G::N / 4), i = 4 * (piece % (G::N / 4));
-                const float *sp = gr + v * G::ROWP + (i / BS) * G::SH + i % BS;
-                if (v0 + v < batch) st4(dx + (v0 + v) * G::N + i, f32x4{sp[0], sp[1], sp[2], sp[3]});
+        f32x4 x[Share::PIECES];
+        Ring<T, 32> ring;
+        TRing<T> tring;
+        // rows past the batch: their gradients are zero, their values a copy of the last row
+        float last = 0.0f;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            int thread = threadIdx.x;
+            asm volatile("" : "+v"(thread) : "v"(last));   // (half of the requests at a time: registers)
+            const Share mine(thread);
+#pragma unroll
+            for (int p = 4 * half; p < 4 * half + 4; ++p) {
+                const bool live = v0 + mine.v(p) < batch;
+                const int64_t at = (live ? v0 + mine.v(p) : batch - 1) * G::N + mine.i;
+                x[p] = ld4(u + at);
+                if (g_in) x[p] *= ld4(g_in + at);
+                f32x4 g = ld4(dy + at);
+                if (!live) g = f32x4{0, 0, 0, 0};
+                put<1>(fw + mine.natural(p), x[p]);
+                put<G::SH>(gr + mine.swapped(p), g);   // dy[s b + r] at (r, s)
+                last = g[0];
             }
-            __syncthreads();
         }
+        preload<T, 32, false>(ring, R, wave, fresh(lane));
+        __syncthreads();
+        if (dL) {
+            stage_from<T, 32, G::SH, false, false>(ring, fw, R, wave, fresh(lane), [](int k) { return k; });   // x -> mid
+            __syncthreads();
+            outer<32, 1>(gr, fw, wave, fresh(lane), [](int r) { return r * G::SH; }, sumL);   // dL[r][s][k]: dy(r, s) x mid(r, k)
+        }
+        preload_t<T>(tring, L, wave, fresh(lane));
+        // (a wave's blocks of the gradient tile are its own in both: no barrier)
+        stage_t<T, 1>(tring, gr, L, wave, fresh(lane), [](int r) { return r * G::SH; });   // dy -> dmid
+        preload_t<T>(tring, R, wave, fresh(lane));
+        __syncthreads();
+        if (dR) {
+            if (dL) {
+                const Share mine(fresh(threadIdx.x));
+#pragma unroll
+                for (int p = 0; p < Share::PIECES; ++p) put<1>(fw + mine.natural(p), x[p]);
+                __syncthreads();
+            }
+            outer<32, G::SH>(gr, fw, wave, fresh(lane), [](int k) { return k; }, sumR);   // dR[k][r][c]: dmid(r, k) x x(c, k)
+        }
+        if (want_dx) {
+            stage_t<T, G::SH>(tring, gr, R, wave, fresh(lane), [](int k) { return k; });   // dmid -> dx at (c, k)
+            __syncthreads();
+            const Share mine(fresh(threadIdx.x));
+#pragma unroll 4
+            for (int p = 0; p < Share::PIECES; ++p) {
+                const int64_t at = (v0 + mine.v(p)) * G::N + mine.i;
+                if (v0 + mine.v(p) >= batch) break;
+                const f32x4 d = get<1>(gr + mine.natural(p));
+                if (dx) st4(dx + at, g_in ? d * ld4(g_in + at) : d);
+                if (dg_in) st4(dg_in + at, d * ld4(u + at));
+            }
+        }
+        __syncthreads();
     }
-    if constexpr (DL) flush<BS>(dL, wave, lane, sum);
+    if (dL) flush<32>(dL, wave, fresh(lane), sumL);
+    if (dR) flush<32>(dR, wave, fresh(lane), sumR);
 }
 
-template <typename T, int BS>
-__global__ __launch_bounds__(Geo<BS>::THREADS, 1) void backward_dr_kernel(const T *__restrict__ x, const T *__restrict__ L,
-                                                                            const T *__restrict__ dy, float *__restrict__ dR, int64_t batch)
+// The first half of the mixer's gradients, y = g_out o M2 (K o s), s = M1 (g_in o u): s again, dg_out, dR2, dL2, dK and
+// ds = dt o K (dt = M2^T (dy o g_out)); backward_kernel takes ds through M1.  Everything between stays in the two tiles, s
+// in registers.  Tiles take their rows channel by channel (row q is sequence q % B of channel q / B) and a workgroup's
+// tiles follow each other, so a channel's dK is summed in registers and K is read once per channel.
+// M2 works on M1's transposed result as it lies, t(s, r) at (r, s): block k' of R2 contracts its own row k' SH of the tile,
+// block r' of L2 the stride SH; dy enters in natural order.
+template <typename T>
+__global__ __launch_bounds__(512, 2) void mixer_backward_kernel(
+    const T *__restrict__ u, const T *__restrict__ K, const T *__restrict__ g_in, const T *__restrict__ g_out, const T *__restrict__ R1,
+    const T *__restrict__ L1, const T *__restrict__ R2, const T *__restrict__ L2, const T *__restrict__ dy, T *__restrict__ ds,
+    float *__restrict__ dK, T *__restrict__ dg_out, float *__restrict__ dR2, float *__restrict__ dL2, int B, int H)
 {
-    typedef Geo<BS> G;
+    typedef Geo<32> G;
     extern __shared__ __attribute__((aligned(16))) float tile[];
     float *fw = tile, *gr = tile + G::TV * G::ROWP;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    f32x4 sum[G::NBW][G::RT][G::RT];
+    Sums sumR, sumL;
+    zero(sumR);
+    zero(sumL);
+    f32x4 dk = {0, 0, 0, 0};
+    int dk_h = -1;
+    auto add_dk = [&]() {
+        if (dk_h >= 0)
 #pragma unroll
-    for (int u = 0; u < G::NBW; ++u)
-#pragma unroll
-        for (int it = 0; it < G::RT; ++it)
-#pragma unroll
-            for (int jt = 0; jt < G::RT; ++jt) sum[u][it][jt] = f32x4{0, 0, 0, 0};
-    const int64_t ntiles = (batch + G::TV - 1) / G::TV;
-    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        load_pair<T, BS>(fw, gr, x, dy, t * G::TV, batch, true);
+            for (int e = 0; e < 4; ++e) atomicAdd(dK + (int64_t)dk_h * G::N + 4 * (threadIdx.x & 255) + e, dk[e]);
+    };
+    const int64_t rows = (int64_t)B * H, ntiles = (rows + G::TV - 1) / G::TV;
+    const int64_t end = ntiles * (blockIdx.x + 1) / gridDim.x;
+    for (int64_t t = ntiles * blockIdx.x / gridDim.x; t < end; ++t) {
+        const int64_t q0 = t * G::TV;
+        const int h0 = (int)(q0 / B), b0 = (int)(q0 - (int64_t)h0 * B);
+        // channel and element offset of piece p; rows past the end: gradients zero, values a copy of the last row
+        auto live = [&](const Share &mine, int p) { return q0 + mine.v(p) < rows; };
+        auto where = [&](const Share &mine, int p, int &h) -> int64_t {
+            const uint32_t v = live(mine, p) ? mine.v(p) : (uint32_t)(rows - 1 - q0), b = b0 + v, over = b / (uint32_t)B;
+            h = h0 + over;
+            return ((int64_t)(b - over * B) * H + h) * G::N + mine.i;
+        };
+        Ring<T, 32> ring;
+        TRing<T> tring;
+        preload<T, 32, false>(ring, R1, wave, fresh(lane));
+        {
+            const Share mine(fresh(threadIdx.x));
+#pragma unroll 4
+            for (int p = 0; p < Share::PIECES; ++p) {
+                int h;
+                const int64_t at = where(mine, p, h);
+                f32x4 a = ld4(u + at), g = ld4(dy + at);
+                if (g_in) a *= ld4(g_in + at);
+                if (g_out) g *= ld4(g_out + at);
+                if (!live(mine, p)) g = f32x4{0, 0, 0, 0};
+                put<1>(fw + mine.natural(p), a);
+                put<1>(gr + mine.natural(p), g);
+            }
+        }
         __syncthreads();
-        stage<T, BS, 1, true>(gr, L, wave, lane, [](int r) { return r * G::SH; });   // dy -> dmid at (r, k)
+        stage_from<T, 32, G::SH, false, false>(ring, fw, R1, wave, fresh(lane), [](int k) { return k; });
+        preload<T, 32, false>(ring, L1, wave, fresh(lane));
         __syncthreads();
-        outer<BS, G::SH>(gr, fw, wave, lane, [](int k) { return k; }, sum);          // dR[k][r][c]: dmid(r, k) x x(c, k)
+        stage_from<T, 32, 1, false, false>(ring, fw, L1, wave, fresh(lane), [](int r) { return r * G::SH; });
+        preload<T, 32, false>(ring, R2, wave, fresh(lane));
+        __syncthreads();
+        f32x4 s[Share::PIECES];
+        {
+            const Share mine(fresh(threadIdx.x));
+#pragma unroll
+            for (int p = 0; p < Share::PIECES; ++p) {
+                int h;
+                where(mine, p, h);
+                s[p] = get<G::SH>(fw + mine.swapped(p));
+                put<G::SH>(fw + mine.swapped(p), s[p] * ld4(K + (int64_t)h * G::N + mine.i));
+            }
+        }
+        __syncthreads();
+        if (dL2 || dg_out) {
+            stage_from<T, 32, 1, false, false>(ring, fw, R2, wave, fresh(lane), [](int k) { return k * G::SH; });   // t -> mid
+            preload<T, 32, false>(ring, L2, wave, fresh(lane));
+            __syncthreads();
+            if (dL2) outer<32, G::SH>(gr, fw, wave, fresh(lane), [](int r) { return r; }, sumL);
+            // (a wave's blocks of either tile are its own in these three: no barrier)
+            if (dg_out) stage_from<T, 32, G::SH, false, false>(ring, fw, L2, wave, fresh(lane), [](int r) { return r; });   // mid -> w
+        }
+        preload_t<T>(tring, L2, wave, fresh(lane));
+        stage_t<T, G::SH>(tring, gr, L2, wave, fresh(lane), [](int r) { return r; });   // dw -> dmid
+        preload_t<T>(tring, R2, wave, fresh(lane));
+        __syncthreads();
+        if (dL2 || dg_out) {
+            if (dg_out) {
+                const Share mine(fresh(threadIdx.x));
+#pragma unroll 4
+                for (int p = 0; p < Share::PIECES; ++p) {
+                    int h;
+                    const int64_t at = where(mine, p, h);
+                    if (live(mine, p)) st4(dg_out + at, get<1>(fw + mine.natural(p)) * ld4(dy + at));
+                }
+                __syncthreads();
+            }
+            if (dR2) {
+                const Share mine(fresh(threadIdx.x));
+#pragma unroll
+                for (int p = 0; p < Share::PIECES; ++p) {
+                    int h;
+                    where(mine, p, h);
+                    put<G::SH>(fw + mine.swapped(p), s[p] * ld4(K + (int64_t)h * G::N + mine.i));
+                }
+                __syncthreads();
+            }
+        }
+        if (dR2) outer<32, 1>(gr, fw, wave, fresh(lane), [](int k) { return k * G::SH; }, sumR);
+        stage_t<T, 1>(tring, gr, R2, wave, fresh(lane), [](int k) { return k * G::SH; });   // dmid -> dt, where t was
+        __syncthreads();
+        {
+            const Share mine(fresh(threadIdx.x));
+#pragma unroll
+            for (int p = 0; p < Share::PIECES; ++p) {
+                int h;
+                const int64_t at = where(mine, p, h);
+                if (!live(mine, p)) break;
+                const f32x4 d = get<G::SH>(gr + mine.swapped(p));
+                st4(ds + at, d * ld4(K + (int64_t)h * G::N + mine.i));
+                if (dK) {
+                    if (h != dk_h) {
+                        add_dk();
+                        dk = f32x4{0, 0, 0, 0};
+                        dk_h = h;
+                    }
+                    dk += d * s[p];
+                }
+            }
+        }
         __syncthreads();
     }
-    flush<BS>(dR, wave, lane, sum);
+    if (dK) add_dk();
+    if (dL2) flush<32>(dL2, wave, fresh(lane), sumL);
+    if (dR2) flush<32>(dR2, wave, fresh(lane), sumR);
 }
 
 // ---- gradients (blocks of 64) ----------------------------------------------------------------------------------
@@ -943,32 +1174,46 @@ static int launch_mixer_t(const void *u, const void *K, const void *g_in, const 
 }
 
 
-template <typename T, int BS>
-static int launch_backward(const void *x, const void *R, const void *L, const void *dy, void *dx, float *dR, float *dL, int64_t batch,
-                           hipStream_t s)
+// a persistent workgroup per compute unit with both tiles
+template <typename Kern>
+static int gradient_grid(Kern kern, int64_t rows, unsigned *grid)
 {
-    typedef Geo<BS> G;
-    const size_t lds = 2 * G::LDS_BYTES;
+    typedef Geo<32> G;
     int dev = 0, ncu = 0;
     MONARCH_HIP_CHECK(hipGetDevice(&dev));
     MONARCH_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    const int64_t ntiles = (batch + G::TV - 1) / G::TV;
-    const unsigned grid = (unsigned)(ntiles < ncu ? ntiles : ncu);   // one workgroup per compute unit
-#define MONARCH_INPL_BWD(KERN, ...)                                                                                        \
-    do {                                                                                                                   \
-        auto kern = KERN;                                                                                                  \
-        MONARCH_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));  \
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(G::THREADS), lds, s, __VA_ARGS__);                                       \
-        MONARCH_HIP_CHECK(hipGetLastError());                                                                              \
-    } while (0)
-    if (dx && dL) MONARCH_INPL_BWD((backward_dx_dl_kernel<T, BS, true, true>), (const T *)x, (const T *)R, (const T *)L, (const T *)dy, (T *)dx, dL, batch);
-    else if (dx) MONARCH_INPL_BWD((backward_dx_dl_kernel<T, BS, true, false>), (const T *)x, (const T *)R, (const T *)L, (const T *)dy, (T *)dx, dL, batch);
-    else if (dL) MONARCH_INPL_BWD((backward_dx_dl_kernel<T, BS, false, true>), (const T *)x, (const T *)R, (const T *)L, (const T *)dy, (T *)dx, dL, batch);
-    if (dR) MONARCH_INPL_BWD((backward_dr_kernel<T, BS>), (const T *)x, (const T *)L, (const T *)dy, dR, batch);
-#undef MONARCH_INPL_BWD
+    MONARCH_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2 * G::LDS_BYTES)));
+    const int64_t ntiles = (rows + G::TV - 1) / G::TV;
+    *grid = (unsigned)(ntiles < ncu ? ntiles : ncu);
     return MONARCH_OK;
 }
 
+template <typename T>
+static int launch_backward32(const void *x, const void *g_in, const void *R, const void *L, const void *dy, void *dx, void *dg_in,
+                             float *dR, float *dL, int64_t batch, hipStream_t s)
+{
+    if (!dx && !dg_in && !dR && !dL) return MONARCH_OK;
+    unsigned grid = 0;
+    if (int rc = gradient_grid(backward_kernel<T>, batch, &grid)) return rc;
+    hipLaunchKernelGGL((backward_kernel<T>), dim3(grid), dim3(512), 2 * Geo<32>::LDS_BYTES, s, (const T *)x, (const T *)g_in, (const T *)R,
+                       (const T *)L, (const T *)dy, (T *)dx, (T *)dg_in, dR, dL, batch);
+    MONARCH_HIP_CHECK(hipGetLastError());
+    return MONARCH_OK;
+}
+
+template <typename T>
+static int launch_mixer_backward32(const void *u, const void *K, const void *g_in, const void *g_out, const void *R1, const void *L1,
+                                   const void *R2, const void *L2, const void *dy, void *ds, void *du, float *dK, void *dg_in,
+                                   void *dg_out, float *dR1, float *dL1, float *dR2, float *dL2, int64_t B, int H, hipStream_t s)
+{
+    unsigned grid = 0;
+    if (int rc = gradient_grid(mixer_backward_kernel<T>, B * H, &grid)) return rc;
+    hipLaunchKernelGGL((mixer_backward_kernel<T>), dim3(grid), dim3(512), 2 * Geo<32>::LDS_BYTES, s, (const T *)u, (const T *)K,
+                       (const T *)g_in, (const T *)g_out, (const T *)R1, (const T *)L1, (const T *)R2, (const T *)L2, (const T *)dy,
+                       (T *)ds, dK, (T *)dg_out, dR2, dL2, (int)B, H);
+    MONARCH_HIP_CHECK(hipGetLastError());
+    return launch_backward32<T>(u, g_in, R1, L1, ds, du, dg_in, dR1, dL1, B * H, s);
+}
 
 template <typename T>
 static int launch_backward64(const void *x, const void *R, const void *L, const void *dy, void *dx, float *dR, float *dL, int64_t batch,
@@ -1072,8 +1317,26 @@ int launch_matmul_backward_inplace(const void *x, const void *R, const void *L, 
     if (bs == 64)
         return dt == MONARCH_F32 ? inpl::launch_backward64<float>(x, R, L, dy, dx, dR, dL, batch, s)
                                  : inpl::launch_backward64<bf16_t>(x, R, L, dy, dx, dR, dL, batch, s);
-    return dt == MONARCH_F32 ? inpl::launch_backward<float, 32>(x, R, L, dy, dx, dR, dL, batch, s)
-                             : inpl::launch_backward<bf16_t, 32>(x, R, L, dy, dx, dR, dL, batch, s);
+    return dt == MONARCH_F32 ? inpl::launch_backward32<float>(x, nullptr, R, L, dy, dx, nullptr, dR, dL, batch, s)
+                             : inpl::launch_backward32<bf16_t>(x, nullptr, R, L, dy, dx, nullptr, dR, dL, batch, s);
+}
+
+// (the kernel counts the rows of a channel in 32 bits)
+bool mixer_backward_inplace_takes(int64_t B, int bs, monarch_dtype dt)
+{
+    return bs == 32 && B > 0 && B < (1 << 30) && (dt == MONARCH_F32 || dt == MONARCH_BF16);
+}
+
+// dK and the factor gradients must have been cleared; ds: scratch of the size of u.
+int launch_mixer_backward_inplace(const void *u, const void *K, const void *g_in, const void *g_out, const void *R1, const void *L1,
+                                  const void *R2, const void *L2, const void *dy, void *ds, void *du, float *dK, void *dg_in,
+                                  void *dg_out, float *dR1, float *dL1, float *dR2, float *dL2, int64_t B, int H, monarch_dtype dt,
+                                  hipStream_t s)
+{
+    return dt == MONARCH_F32 ? inpl::launch_mixer_backward32<float>(u, K, g_in, g_out, R1, L1, R2, L2, dy, ds, du, dK, dg_in, dg_out,
+                                                                    dR1, dL1, dR2, dL2, B, H, s)
+                             : inpl::launch_mixer_backward32<bf16_t>(u, K, g_in, g_out, R1, L1, R2, L2, dy, ds, du, dK, dg_in, dg_out,
+                                                                     dR1, dL1, dR2, dL2, B, H, s);
 }
 
 // rows of a multiple of 4 elements (16-byte pieces of fp32 rows, 8-byte pieces of bf16 rows)

@@ -104,3 +104,29 @@ def test_empty_batch_with_null_inputs_through_the_raw_abi(mm):
     torch.cuda.synchronize()
     for name, t in outs.items():
         assert float(t.abs().max()) == 0.0, name
+
+
+@pytest.mark.parametrize("B,H,gates,bf16", [(1, 40, (True, True), False), (3, 11, (False, True), False), (16, 3, (True, False), False),
+                                            (17, 2, (False, False), False), (37, 3, (True, True), True), (40, 128, (True, True), False)])
+def test_blocks_of_32_channel_by_channel(mm, B, H, gates, bf16):
+    # tiles of 16 rows in the order of the channels: channels that are a part of a tile, that end inside one and that take
+    # several, a last tile of 1 to 15 rows, and (40 x 128) workgroups with more than one tile and channels shared by two
+    announce("mixer backward b=32 B, H, gates, bf16", B, H, gates, bf16)
+    w = workloads.mixer_inputs(B, H, 32, seed=B + H, gates=gates, bf16=bf16)
+    _check(mm, w, _dy(w, 6, bf16), TOL_BF16 if bf16 else TOL_F32, bf16=bf16)
+
+
+@pytest.mark.parametrize("asked", GRADS)
+def test_blocks_of_32_one_output_alone(mm, asked):
+    announce("mixer backward b=32, one output:", asked)
+    w = workloads.mixer_inputs(5, 7, 32, seed=3)
+    dy = _dy(w, 7)
+    want = layer.mixer_backward(*(w[k] for k in KEYS), dy)[asked]
+    t = [dev(w[k]) for k in KEYS] + [dev(dy)]
+    out = torch.full(want.shape, 7.0, device="cuda")
+    lib = mm.raw()
+    ws = torch.empty(lib.monarch_mixer_backward_workspace_bytes(5, 7, 32, mm.F32), dtype=torch.uint8, device="cuda")
+    rc = lib.monarch_mixer_backward(*(v.data_ptr() for v in t), *(out.data_ptr() if name == asked else None for name in GRADS),
+                                    5, 7, 32, mm.F32, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0, lib.monarch_last_error()
+    assert rel_l2(host(out), want) <= TOL_F32
