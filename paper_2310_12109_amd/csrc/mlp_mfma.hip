@@ -465,7 +465,7 @@ template <typename E, int KS, int ACT, int NT>
 __global__ __launch_bounds__(256, 1) void mlp_order1_stream_kernel(
     const E *__restrict__ x, E *__restrict__ y, int64_t tokens, int d, int d_hidden, int nb,
     const E *__restrict__ W1, const E *__restrict__ b1, const E *__restrict__ W2,
-    const E *__restrict__ b2, int b1_interleaved)
+    const E *__restrict__ b2, int b1_interleaved, int by_block)
 {
     constexpr int DIN = 32 * KS, MT = 2 * KS, OPS = 4 * KS;   // operand pieces (64 lanes x 16 B) per hidden chunk
     constexpr int ring = ring_slots(KS);
@@ -473,8 +473,8 @@ __global__ __launch_bounds__(256, 1) void mlp_order1_stream_kernel(
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, l16 = lane & 15, kg = lane >> 4;
-    const int blk = blockIdx.y;
-    const int64_t t0 = (int64_t)blockIdx.x * (64 * NT) + 16 * NT * wave;   // NT column tiles of 16 tokens per wave
+    const int blk = by_block ? blockIdx.x : blockIdx.y;   // see mlp_by_block
+    const int64_t t0 = (int64_t)(by_block ? blockIdx.y : blockIdx.x) * (64 * NT) + 16 * NT * wave;   // NT column tiles of 16 tokens per wave
     const int dh = d_hidden / nb, nch = dh / 32;
     const E *W1b = W1 + (size_t)blk * dh * DIN;   // [dh][DIN]
     const E *W2b = W2 + (size_t)blk * DIN * dh;   // [DIN][dh]
@@ -624,7 +624,7 @@ template <typename E, int KS, int ACT>
 __global__ __launch_bounds__(256, 1) void mlp_order1_split_kernel(
     const E *__restrict__ x, E *__restrict__ y, int64_t tokens, int d, int d_hidden, int nb,
     const E *__restrict__ W1, const E *__restrict__ b1, const E *__restrict__ W2,
-    const E *__restrict__ b2, int b1_interleaved)
+    const E *__restrict__ b2, int b1_interleaved, int by_block)
 {
     constexpr int DIN = 32 * KS, MT = 2 * KS, ITEM = 2 * KS;   // ITEM: 1 KB pieces of one ring part
     extern __shared__ __attribute__((aligned(16))) uint4 lds_split[];   // [3 slots][4 waves][ITEM * 64], bias [dh]
@@ -633,8 +633,8 @@ __global__ __launch_bounds__(256, 1) void mlp_order1_split_kernel(
     const int lane = tid & 63, l16 = lane & 15, kg = lane >> 4;
     const int frow = lane >> 2, fkg = lane & 3;   // the operand entry this lane fetches
     const int rd = 4 * l16 + kg;                  // where the entry this lane uses sits in a piece
-    const int blk = blockIdx.y;
-    const int64_t t0 = (int64_t)blockIdx.x * TOK;
+    const int blk = by_block ? blockIdx.x : blockIdx.y;   // see mlp_by_block
+    const int64_t t0 = (int64_t)(by_block ? blockIdx.y : blockIdx.x) * TOK;
     const int dh = d_hidden / nb, nch = dh / 32;
     const int nmine = wave < nch ? (nch - wave + 3) / 4 : 0;   // chunks wave, wave + 4, ...
     const E *W1b = W1 + (size_t)blk * dh * DIN;   // [dh][DIN]
@@ -885,6 +885,13 @@ bool mlp_mfma_order1_supported(int d, int d_hidden, int nb, monarch_dtype dt)
 
 namespace {
 
+// Workgroups go to the eight XCDs in turn.  With the blocks fastest an XCD meets only the blocks of its residue (one of four,
+// one of eight) and fetches only their weights into its L2, with the tiles fastest every XCD fetches all of them.  That
+// pays where the weights are large against a L2 of 4 MB: 768 -> 3072 in 4 blocks (2.4 MB), us, tiles first against blocks first:
+// 700 tokens 18.8 : 17.3, 4096 20.4 : 19.7, 16384 74.7 : 72.4; 1536 -> 6144 in 8 (4.7 MB): 1000 tokens 19.4 : 17.8.  512 -> 2048
+// in 8 (0.5 MB) is as fast either way, 1024 -> 4096 in 16 (1 MB) slower (9.8 : 10.1).  Grids of up to 65535 tiles.
+bool mlp_by_block(int d, int dh_blk, int64_t tiles) { return (int64_t)4 * d * dh_blk >= 2 << 20 && tiles <= 65535; }
+
 template <typename E>
 int launch_typed(const void *x, void *y, int64_t tokens, int d, int d_hidden, int nb, const void *W1,
                  const void *b1, const void *W2, const void *b2, int act, int b1_interleaved, hipStream_t s)
@@ -941,7 +948,8 @@ int launch_typed(const void *x, void *y, int64_t tokens, int d, int d_hidden, in
         // that still gives every compute unit a workgroup.
         const int ntv = tokens * nb >= (int64_t)512 * ncu ? 4 : 2;
         const int64_t wtiles = (tokens + 64 * ntv - 1) / (64 * ntv);
-        const dim3 sgrid((unsigned)wtiles, (unsigned)nb);
+        const int by_block = mlp_by_block(d, dh_blk, wtiles);
+        const dim3 sgrid = by_block ? dim3((unsigned)nb, (unsigned)wtiles) : dim3((unsigned)wtiles, (unsigned)nb);
         const size_t str_lds = (size_t)mlp1::ring_slots(din / 32) * (din / 8) * 1024 + (size_t)dh_blk * 2;
 #define MONARCH_LAUNCH_STR(KSV, ACTV, NTV)                                                                       \
     do {                                                                                                         \
@@ -950,7 +958,7 @@ int launch_typed(const void *x, void *y, int64_t tokens, int d, int d_hidden, in
                                               (int)str_lds));                                                    \
         hipLaunchKernelGGL(kern, sgrid, dim3(256), str_lds, s, (const E *)x, (E *)y, tokens, d,        \
                            d_hidden, nb, (const E *)W1, (const E *)b1, (const E *)W2,             \
-                           (const E *)b2, b1_interleaved);                                                  \
+                           (const E *)b2, b1_interleaved, by_block);                                                  \
     } while (0)
 #define MONARCH_LAUNCH_STR_NT(KSV, ACTV)                      \
     do {                                                      \
@@ -979,15 +987,18 @@ int launch_typed(const void *x, void *y, int64_t tokens, int d, int d_hidden, in
     }
     const size_t split_lds = mlp1::split_lds_bytes(din / 32, dh_blk);
     if (split_lds <= 160 * 1024) {
+        // (order 2: the launch before left a tile's tokens in the L2 of its XCD, 45.6 against 47.9 us at 4096 tokens of 768)
+        const int by_block = !b1_interleaved && mlp_by_block(d, dh_blk, tiles);
+        const dim3 pgrid = by_block ? dim3((unsigned)nb, (unsigned)tiles) : grid;
 #define MONARCH_LAUNCH_SPL(KSV, ACTV)                                                                            \
     do {                                                                                                         \
         auto kern = mlp1::mlp_order1_split_kernel<E, KSV, ACTV>;                                                    \
         if (split_lds > 48 * 1024)                                                                               \
             MONARCH_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, \
                                                   (int)split_lds));                                              \
-        hipLaunchKernelGGL(kern, grid, dim3(256), split_lds, s, (const E *)x, (E *)y, tokens, d,       \
+        hipLaunchKernelGGL(kern, pgrid, dim3(256), split_lds, s, (const E *)x, (E *)y, tokens, d,       \
                            d_hidden, nb, (const E *)W1, (const E *)b1, (const E *)W2,             \
-                           (const E *)b2, b1_interleaved);                                                  \
+                           (const E *)b2, b1_interleaved, by_block);                                                  \
     } while (0)
 #define MONARCH_LAUNCH_SPL_ACT(KSV)                     \
     do {                                                \
