@@ -350,7 +350,7 @@ def widening_cases():
                     return lambda: binding.monarch_matmul_backward(x, R, L, dy)
                 return one
             add("matmul_backward_%s_b%d_batch_%d" % (dn, b, rows), "gradients of the order-2 Monarch matmul N=%d, %s, batch %d" % (N, dn, rows),
-                dn, "inpl::backward_dx_dl_kernel + backward_dr_kernel" if b == 32 else "inpl::backward64_dx_kernel + 2 x backward64_factor_kernel",
+                dn, "inpl::backward_kernel" if b == 32 else "inpl::backward64_dx_kernel + 2 x backward64_factor_kernel",
                 3 * rows * N * es + 2 * b ** 3 * (es + 4), rows * 10.0 * N * b, rows * N, mk_mm_bwd_b)
             add("mixer_%s_b%d_B%d" % (dn, b, B), "learned-Monarch sequence mixer N=%d, B=%d H=768, %s" % (N, B, dn), dn,
                 "inpl::mixer_kernel<%d>" % b, (4 * rows * N + 768 * N + 4 * b ** 3) * es, rows * 8.0 * N * b, rows * N, mk_mixer_b)
@@ -522,12 +522,10 @@ def widening_cases():
                 return lambda: binding.monarch_hyena_layer(u, W_in, b_in, k_short, k_long, W_out, b_out, (64, 32), ws=ws, out=y)
             return one
         add("hyena_layer_%s_B8_n1024_d768" % dn, "gated-convolution layer (projections, short convs, gated long conv) B=8 n=1024 d=768, %s" % dn,
-            dn, "rocBLAS GEMMs + short_conv_kernel + conv2048 kernel", (2 * B * n * d + 4 * d * d + d * n) * es,
+            dn, "rocBLAS GEMMs + short_conv_kernel + " + ("conv2048 kernel" if dn == "bf16" else "cfft::conv_kernel"), (2 * B * n * d + 4 * d * d + d * n) * es,
             8.0 * B * n * d * d, B * n * d, mk_hy, bound="mfma", mfma_peak=MFMA_BF16_TFLOPS if dn == "bf16" else MFMA_F32_TFLOPS)
 
-    # the same layer with heads of 16 features (the head dimension of the paper's causal models): 256 long convolutions
-    # per head and batch entry
-    from paper_2310_12109_amd import costmodel
+    # the same layer with heads of 16 features (the head dimension of the paper's causal models)
     for dn in ("bf16", "f32"):
         es = 4 if dn == "f32" else 2
         B, n, d, dh = 8, 1024, 768, 16
@@ -547,9 +545,9 @@ def widening_cases():
             return one
         add("hyena_heads_layer_%s_B8_n1024_d768_dh16" % dn,
             "gated-convolution layer with heads of 16 features B=8 n=1024 d=768, %s" % dn, dn,
-            "rocBLAS GEMMs + short_conv_kernel + conv2048 kernel (outer products on its loads) + heads_sum_kernel" if dn == "bf16"
-            else "rocBLAS GEMMs + short_conv_kernel + heads_outer_kernel + conv2048 kernel + heads_sum_kernel",
-            (2 * B * n * d + 4 * d * d + (d // dh) * n) * es, 8.0 * B * n * d * d + costmodel.conv_executed_flops(B * dh * dh, d // dh, (64, 32)),
+            "rocBLAS GEMMs + hheads::short_conv_kernel + hheads::heads_kernel",
+            # two products of inner length dh and one multiplication for each pair of positions s <= t of a head
+            (2 * B * n * d + 4 * d * d + (d // dh) * n) * es, 8.0 * B * n * d * d + B * (d // dh) * (n * n / 2) * (4.0 * dh + 1),
             B * n * d, mk_hyh, bound="mfma",
             mfma_peak=MFMA_BF16_TFLOPS if dn == "bf16" else MFMA_F32_TFLOPS)
 
@@ -575,7 +573,7 @@ def all_cases():
     return [
         ConvCase("c2_conv_bf16", "c2_conv", True, "conv2048_kernel<bf16>", "hbm"),
         MatmulCase(),
-        ConvCase("c2_conv_f32", "c2_conv", False, "conv2048_f32_kernel", "mfma", MFMA_F32_TFLOPS),
+        ConvCase("c2_conv_f32", "c2_conv", False, "cfft::conv_kernel", "hbm"),
         ConvCase("c3a_conv_bf16", "c3a_conv", True, "conv256_bf16_kernel", "hbm"),
         MlpCase("c3b_mlp_order1", "c3b_mlp", 1, "mlp_order1_split_kernel", "mfma"),
         MlpCase("c3b_mlp_order2", "c3b_mlp", 2, "factor_kernel + mlp_order1 + factor_kernel", "mfma"),
