@@ -84,13 +84,13 @@ struct Ring {
 };
 
 template <typename T, int BS, bool TRANS>
-__device__ __forceinline__ void request(const T *__restrict__ src, int item, int wave, int lane, f32x4 (&dst)[Ring<T, BS, TRANS>::WV])
+__device__ __forceinline__ void request_at(const T *__restrict__ src, int blk, int rt, int lane, f32x4 (&dst)[Ring<T, BS, TRANS>::WV])
 {
     typedef Geo<BS> G;
     constexpr int WV = Ring<T, BS, TRANS>::WV;
     const int l16 = lane & 15, kg = lane >> 4;
     // (a uniform address per item and one lane offset for all items and matrices: no address registers to keep)
-    const T *at = src + ((size_t)(wave * G::NBW + item / G::RT) * BS + (TRANS ? 0 : 16 * (item % G::RT))) * BS + (TRANS ? 16 * (item % G::RT) : 0);
+    const T *at = src + ((size_t)blk * BS + (TRANS ? 0 : 16 * rt)) * BS + (TRANS ? 16 * rt : 0);
     if constexpr (TRANS) {   // lane (row i, group g) takes W[blk][(b/4) g + j][i]: loads run along i across a group's lanes
         const uint32_t off = G::Q * kg * BS + l16;
 #pragma unroll
@@ -106,6 +106,13 @@ __device__ __forceinline__ void request(const T *__restrict__ src, int item, int
 #pragma unroll
         for (int p = 0; p < WV; ++p) dst[p] = ld4(at + 4 * p + off);
     }
+}
+
+template <typename T, int BS, bool TRANS>
+__device__ __forceinline__ void request(const T *__restrict__ src, int item, int wave, int lane, f32x4 (&dst)[Ring<T, BS, TRANS>::WV])
+{
+    typedef Geo<BS> G;
+    request_at<T, BS, TRANS>(src, wave * G::NBW + item / G::RT, item % G::RT, lane, dst);
 }
 
 template <typename T, int BS, bool TRANS>
@@ -276,6 +283,104 @@ __global__ __launch_bounds__(Geo<BS>::THREADS, 4) void matmul_kernel(const T *__
             if (v0 + v < batch) st4s(y + (v0 + v) * G::N + m, f32x4{sp[0], sp[G::SH], sp[2 * G::SH], sp[3 * G::SH]});
         }
         __syncthreads();
+    }
+}
+
+// NT row tiles of one block from row row0 on, the block's inputs at e (stride SK), the matrices in registers: the products
+// of stage_from, in its order
+template <typename T, int BS, int SK, bool EXACT, int NT>
+__device__ __forceinline__ void block_products(float *e, const f32x4 (&w)[NT][Ring<T, BS>::WV], int row0, int l16, int kg)
+{
+    typedef Geo<BS> G;
+    f32x4 acc[NT];
+    if constexpr (Ring<T, BS>::HALF) {
+        constexpr int CH = BS / 32, PARTS = EXACT ? 1 : 3;
+        h16::op8 b[CH][3];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            float x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = e[(32 * c + 8 * kg + j) * SK];
+            if constexpr (EXACT) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) b[c][0][j] = high_halves(__float_as_uint(x[2 * j]), __float_as_uint(x[2 * j + 1]));
+            } else split3(x, b[c]);
+        }
+#pragma unroll
+        for (int rt = 0; rt < NT; ++rt) {
+            acc[rt] = f32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int part = PARTS - 1; part >= 0; --part)
+#pragma unroll
+                for (int c = 0; c < CH; ++c) acc[rt] = h16::mfma<bf16_t>(__builtin_bit_cast(h16::op8, w[rt][c]), b[c][part], acc[rt]);
+        }
+    } else {
+        float bv[G::Q];
+#pragma unroll
+        for (int j = 0; j < G::Q; ++j) bv[j] = e[(G::Q * kg + j) * SK];
+#pragma unroll
+        for (int rt = 0; rt < NT; ++rt) {
+            acc[rt] = f32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < G::Q; ++j) acc[rt] = mfma(w[rt][j >> 2][j & 3], bv[j], acc[rt]);
+        }
+    }
+    if (l16 < G::TV) {
+#pragma unroll
+        for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) e[(row0 + 16 * rt + 4 * kg + r) * SK] = acc[rt][r];
+    }
+}
+
+// The product for few rows, a tile divided over BS / 16 workgroups: each forms 16 of the middle indices r, rows r of every
+// block of R, and takes them through its 16 blocks of L, so that nothing is formed twice and nothing is summed across
+// workgroups.  A workgroup of matmul_kernel reads both matrices whole (2 MB in fp32 at b = 64) and that is all of its time
+// where the tiles leave compute units idle; here a part of it, requested at once.  Neighbouring workgroups are different
+// parts: an XCD fetches one or two of them.  Results are those of matmul_kernel bit for bit.
+template <typename T, int BS>
+__global__ __launch_bounds__(Geo<BS>::THREADS, Geo<BS>::THREADS / 256) void matmul_few_kernel(const T *__restrict__ x, const T *__restrict__ R,
+                                                                                            const T *__restrict__ L, T *__restrict__ y,
+                                                                                            int64_t batch)
+{
+    typedef Geo<BS> G;
+    typedef Ring<T, BS> Rg;
+    constexpr int NB = 16 / G::WAVES;                        // blocks of L of a wave
+    constexpr bool EARLY = BS == 32 || Rg::HALF;             // registers for both matrices
+    extern __shared__ __attribute__((aligned(16))) float tile[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15, kg = lane >> 4;
+    const int part = blockIdx.x % G::RT;
+    const int64_t v0 = (int64_t)(blockIdx.x / G::RT) * G::TV;
+    f32x4 wr[G::NBW][1][Rg::WV], wl[NB][G::RT][Rg::WV];
+    auto request_l = [&]() {
+#pragma unroll
+        for (int i = 0; i < NB * G::RT; ++i)
+            request_at<T, BS, false>(L, 16 * part + wave * NB + i / G::RT, i % G::RT, lane, wl[i / G::RT][i % G::RT]);
+    };
+#pragma unroll
+    for (int u = 0; u < G::NBW; ++u) request_at<T, BS, false>(R, wave * G::NBW + u, part, lane, wr[u][0]);
+    if constexpr (EARLY) request_l();
+    for (int piece = threadIdx.x; piece < G::TV * G::N / 4; piece += G::THREADS) {
+        const int v = piece / (G::N / 4), i = 4 * (piece % (G::N / 4));
+        int64_t r = v0 + v;
+        if (r >= batch) r = batch - 1;   // (rows past the end: computed, never stored)
+        const f32x4 val = ld4(x + r * G::N + i);
+        float *d = tile + v * G::ROWP + (i / BS) * G::SH + i % BS;
+        d[0] = val[0]; d[1] = val[1]; d[2] = val[2]; d[3] = val[3];
+    }
+    __syncthreads();
+    float *mine = tile + (l16 & (G::TV - 1)) * G::ROWP;
+#pragma unroll
+    for (int u = 0; u < G::NBW; ++u) block_products<T, BS, G::SH, true, 1>(mine + wave * G::NBW + u, wr[u], 16 * part, l16, kg);
+    if constexpr (!EARLY) request_l();
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NB; ++u) block_products<T, BS, 1, false, G::RT>(mine + (16 * part + wave * NB + u) * G::SH, wl[u], 0, l16, kg);
+    __syncthreads();
+    for (int piece = threadIdx.x; piece < G::TV * BS * 4; piece += G::THREADS) {   // four r of one s
+        const int v = piece / (BS * 4), s = piece / 4 % BS, r = 16 * part + 4 * (piece % 4);
+        const float *sp = tile + v * G::ROWP + r * G::SH + s;
+        if (v0 + v < batch) st4(y + (v0 + v) * G::N + s * BS + r, f32x4{sp[0], sp[G::SH], sp[2 * G::SH], sp[3 * G::SH]});
     }
 }
 
@@ -1139,9 +1244,15 @@ template <typename T, int BS>
 static int launch_matmul(const void *x, const void *R, const void *L, void *y, int64_t batch, hipStream_t s)
 {
     typedef Geo<BS> G;
+    const int64_t ntiles = (batch + G::TV - 1) / G::TV;
     int64_t grid = 0;
-    if (int rc = grid_for<BS>((batch + G::TV - 1) / G::TV, &grid)) return rc;
-    auto kern = matmul_kernel<T, BS>;
+    if (int rc = grid_for<BS>(ntiles, &grid)) return rc;
+    // a compute unit for every part; matmul_kernel : matmul_few_kernel, us, at that line and past it: b = 64, 512 rows, fp32
+    // 68.3 : 25.3, bf16 35.5 : 16.1 (one row 64.8 : 21.6, 31.1 : 12.3); b = 32, 2048 rows, fp32
+    // 14.9 : 11.3, bf16 9.4 : 9.2, 4096 rows 15.8 : 17.6, 10.0 : 11.5
+    const bool few = grid == ntiles && ntiles * G::RT <= 256;
+    if (few) grid = ntiles * G::RT;
+    auto kern = few ? matmul_few_kernel<T, BS> : matmul_kernel<T, BS>;
     MONARCH_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS_BYTES));
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(G::THREADS), G::LDS_BYTES, s, (const T *)x, (const T *)R, (const T *)L, (T *)y, batch);
     MONARCH_HIP_CHECK(hipGetLastError());

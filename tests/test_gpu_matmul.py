@@ -129,6 +129,22 @@ def test_large_batch_sampled(mm):
     assert rel_l2(got, oracle.matmul(xs, w["R"], w["L"])) <= TOL_F32
 
 
+# few rows: a tile divided over b / 16 workgroups, up to a compute unit for every part (128 tiles of 16 rows, 64 of 8), and the
+# first size past that
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("b,batch", [(32, 1), (32, 17), (32, 2048), (32, 2049), (64, 1), (64, 9), (64, 512), (64, 513)])
+def test_few_rows_divided_over_workgroups(mm, b, batch, bf16):
+    announce("matmul few rows", b, batch, bf16)
+    g = torch.Generator().manual_seed(b + batch)
+    x, R, L = (torch.randn(*shape, generator=g).mul(scale).to(torch.bfloat16 if bf16 else torch.float32)
+               for shape, scale in (((batch, b * b), 1.0), ((b, b, b), b ** -0.5), ((b, b, b), b ** -0.5)))
+    got = mm.monarch_matmul(x.cuda(), R.cuda(), L.cuda()).cpu().double().numpy()
+    rows = np.unique(np.r_[0, batch - 1, np.random.default_rng(2).integers(0, batch, 40)])
+    want = oracle.matmul(x[rows].float().numpy(), R.float().numpy(), L.float().numpy())
+    assert rel_l2(got[rows], want) <= (2.0 ** -8 if bf16 else TOL_F32)   # bf16: the rounding of the result
+    assert (np.linalg.norm(got[rows] - want, axis=1) / np.linalg.norm(want, axis=1)).max() <= (2.0 ** -8 if bf16 else TOL_F32)
+
+
 # bf16 blocks of 32 and 64: the tile's fp32 values meet the bf16 matrices as three bf16 parts.  A whole and a partial tile,
 # magnitudes over sixty decades (the parts of a value lie up to 2^-24 below it), and one infinity and one NaN, which
 # must come out where plain floating point puts them and nowhere else
