@@ -11,7 +11,8 @@
 // multiplications instead of the 256 multiply-adds of the dense factor, which is why this unit beats the fp32
 // matrix instruction here (64 x 64 in two MFMA passes: 70 us of matrix products alone at the shape below; its error
 // is also smaller).  Between the factors the values change threads through LDS: one exchange inside a wave (a k1 belongs to
-// R neighbouring lanes), one across the slot, in padded layouts without bank conflicts: two barriers per pair of rows.
+// R neighbouring lanes), one across the slot, in padded layouts without bank conflicts: two barriers per pair of rows, and one
+// after the kernel's spectrum, whose transform leaves the waves at work on their rows of LDS.
 // B = 7, H = 384, n = 2004, N = 4096, both gates: 34 us (six MFMA passes through memory: 171), of it 17 us the rows at
 // the rate of a copy and about as much vector instructions (1300 per thread and pair, 3 waves per SIMD); the two
 // overlap only between workgroups.  B = 8, H = 768, n = 1024, N = 2048: 36 us (a 64 x 32 MFMA kernel: 75).  Three
@@ -148,7 +149,9 @@ __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_
     const int pairs = (B + 1) / 2;
     __syncthreads();
 
-    // forward transform of v (value n = t + M j in v[j]) into z[unit][m R + k3]
+    // forward transform of v (value n = t + M j in v[j]) into z[unit][m R + k3].  It begins by storing to every k1 row of the
+    // slot's buffer, so no wave of the slot may still be at work on a row there; it ends while the waves are, each on
+    // its own rows.
     auto forward = [&](float2 (&v)[A], float2 (&z)[U][16]) {
         dft<A, HALF>(v);
 #pragma unroll
@@ -217,7 +220,8 @@ __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_
             for (int j = 0; j < 16; ++j) mine[t2 + R * j] = x[j];
         }
         __syncthreads();
-        // (a thread reads the places that it will itself write in the next transform: no barrier before that one)
+        // (the rows are free, and a thread reads just the places that it will itself write in the next forward transform: no
+        // barrier before that one)
 #pragma unroll
         for (int k1 = 0; k1 < A; ++k1) v[k1] = buf[k1 * P + t];
 #pragma unroll
@@ -236,6 +240,7 @@ __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_
     for (int w = 0; w < U; ++w)
 #pragma unroll
         for (int e = 0; e < 16; ++e) kf[w][e] = make_float2(kf[w][e].x * (1.0f / G::N), kf[w][e].y * (1.0f / G::N));
+    __syncthreads();   // forward after forward: every wave has left its rows (all slots, whether live or not)
 
     for (int p = split; p - split < pairs; p += splits) {   // as many rounds for every slot of the workgroup
         const bool live = live_item && p < pairs;

@@ -287,3 +287,24 @@ def test_fp32_rows_in_registers(mm, B, H, n, klen, factors, gates, causal):
         w["g_out" if gates == "in" else "g_in"] = None
     # a transform of radix 2..32 steps in fp32: error about 2^-24 sqrt(log2 N), far below the bound of the fp32 paths
     assert rel_l2(_run(mm, w, factors, False, causal), _oracle(w, nfft, causal)) <= TOL_F32
+
+
+# rows so short that most waves of a workgroup load nothing between the kernel's transform and the first pair's: a slot of
+# several waves (lengths 2048 to 8192), its kernel long and short, more pairs than one per slot; every call the same bits
+@pytest.mark.parametrize("factors", [(64, 32), (64, 64), (128, 64)])
+@pytest.mark.parametrize("n,klen", [(1, 1), (1, 1024), (17, 17), (64, 1000)])
+def test_fp32_short_rows_behind_the_kernel_spectrum(mm, factors, n, klen):
+    announce("conv fp32 short rows", factors, n, klen)
+    nfft = int(np.prod(factors))
+    w = workloads.conv_inputs(5, 600, n, seed=n + klen, gates="none")
+    w["k"] = np.random.default_rng(klen).standard_normal((600, klen)).astype(np.float32)
+    want = _oracle(w, nfft, False)
+    first = _run(mm, w, factors, False, False)
+    # Each row by itself, as a wrong spectrum of k is a wrong channel.  The transforms are accurate in the 2-norm, about
+    # 2^-24 sqrt(log2 N) each: three of them are below 1e-6 of the largest |F k| times the norm of the rows that share a transform.
+    gain = np.abs(np.fft.fft(w["k"].astype(np.float64), nfft)).max(axis=1)
+    rows = np.linalg.norm(w["u"].astype(np.float64), axis=2)
+    for b in range(5):
+        pair = np.hypot(rows[b], rows[min(b ^ 1, 4)])
+        assert (np.linalg.norm(first[b] - want[b], axis=1) <= 1e-6 * gain * pair).all(), b
+    assert np.array_equal(first, _run(mm, w, factors, False, False))
