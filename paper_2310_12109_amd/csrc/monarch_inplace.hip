@@ -124,32 +124,84 @@ __device__ __forceinline__ void preload(Ring<T, BS, TRANS> &ring, const T *__res
     for (int d = 0; d < Rg::DEPTH && d < Rg::ITEMS; ++d) request<T, BS, TRANS>(W, d, wave, lane, ring.w[d]);
 }
 
+// The same value, unknown to the compiler: addresses derived from it are formed at their use instead of being kept in
+// registers over a persistent workgroup's tiles (with the sums of the gradients there is no room for them: 556 bytes of spills
+// a lane).
+__device__ __forceinline__ int fresh(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Eight fp32 values as three bf16 operands, x = hi + mid + lo exactly (8 + 8 + 8 significant bits; each part is the
-// remainder of the one before cut to its upper 16 bits).  Infinities and NaN are their own high parts.
+// remainder of the one before cut to its upper 16 bits) for every finite x.  The mid part of an infinity is a NaN, and an
+// infinite weight meets parts that are zero: such products come out as NaN and are formed again, see plain_where_nan.
 __device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 __device__ __forceinline__ void split3(const float (&x)[8], h16::op8 (&p)[3])
 {
-    uint32_t hi[8], mid[8], lo[8], top = 0;
+    uint32_t hi[8], mid[8], lo[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const uint32_t v = __float_as_uint(x[j]);
-        top = top > (v & 0x7fffffffu) ? top : (v & 0x7fffffffu);
         hi[j] = v;
         const float r = x[j] - __uint_as_float(v & 0xffff0000u);
         mid[j] = __float_as_uint(r);
         lo[j] = __float_as_uint(r - __uint_as_float(mid[j] & 0xffff0000u));
     }
-    if (__builtin_expect(top >= 0x7f800000u, 0)) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if ((hi[j] & 0x7fffffffu) >= 0x7f800000u) {
-                if ((hi[j] & 0x7fffffffu) > 0x7f800000u) hi[j] |= 0x00400000u;   // (a NaN stays one without its low half)
-                mid[j] = lo[j] = 0;
-            }
-    }
     p[0] = h16::op8{high_halves(hi[0], hi[1]), high_halves(hi[2], hi[3]), high_halves(hi[4], hi[5]), high_halves(hi[6], hi[7])};
     p[1] = h16::op8{high_halves(mid[0], mid[1]), high_halves(mid[2], mid[3]), high_halves(mid[4], mid[5]), high_halves(mid[6], mid[7])};
     p[2] = h16::op8{high_halves(lo[0], lo[1]), high_halves(lo[2], lo[3]), high_halves(lo[4], lo[5]), high_halves(lo[6], lo[7])};
+}
+
+// whether a product of the wave is a NaN (the sum of a lane's products tells it; one of opposite infinities only costs time)
+template <int NT>
+__device__ __forceinline__ bool any_nan(const f32x4 (&a)[NT])
+{
+    f32x4 t = a[0];
+#pragma unroll
+    for (int rt = 1; rt < NT; ++rt) t += a[rt];
+    const float sum = (t[0] + t[1]) + (t[2] + t[3]);
+    return __builtin_amdgcn_ballot_w64(sum != sum) != 0;
+}
+
+// The products of a block of bf16 weights again, its inputs still in place at e: those that are NaN by the three parts as the
+// fp32 instruction forms them, so that infinities and NaN of the rows and of the weights come out as plain floating point has
+// them, and the others as they were.  A block that holds a NaN takes this way, for rows and weights without them one test per
+// block (it replaced a test of every value in split3).
+template <int BS, int SK>
+__device__ __forceinline__ void plain_where_nan(float *e, const bf16_t *__restrict__ W, int blk, int lane)
+{
+    typedef Geo<BS> G;
+    constexpr int CH = BS / 32;
+    const int l16 = lane & 15, kg = lane >> 4;
+    float x[CH][8];
+    h16::op8 b[CH][3];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[c][j] = e[(32 * c + 8 * kg + j) * SK];
+        split3(x[c], b[c]);
+    }
+#pragma unroll 1
+    for (int rt = 0; rt < G::RT; ++rt) {
+        f32x4 w[CH], a = {0, 0, 0, 0}, plain = {0, 0, 0, 0};
+        request_at<bf16_t, BS, false>(W, blk, rt, lane, w);
+#pragma unroll
+        for (int part = 2; part >= 0; --part)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) a = h16::mfma<bf16_t>(__builtin_bit_cast(h16::op8, w[c]), b[c][part], a);
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t pair = __float_as_uint(w[c][j >> 1]);
+                plain = mfma(j & 1 ? h16::hi32<bf16_t>(pair) : h16::lo32<bf16_t>(pair), x[c][j], plain);
+            }
+        if (l16 < G::TV) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) e[(16 * rt + 4 * kg + r) * SK] = a[r] != a[r] ? plain[r] : a[r];
+        }
+    }
 }
 
 // One factor in place, its first items in the ring.  Block blk contracts the digit that has stride SK; its other digit
@@ -164,6 +216,7 @@ __device__ __forceinline__ void stage_from(Ring<T, BS, TRANS> &ring, float *tile
     const int l16 = lane & 15, kg = lane >> 4;
     float *mine = tile + (l16 & (G::TV - 1)) * G::ROWP;
     float anchor = 0.0f;
+    uint32_t again = 0;   // the wave's blocks with a NaN among their products: left as they were for plain_where_nan
     // (the pointer passes through an empty asm that names the latest result, so that the compiler keeps each
     // request where it is written instead of hoisting all of a stage's loads to its top)
     auto next = [&](int item) {
@@ -218,6 +271,12 @@ __device__ __forceinline__ void stage_from(Ring<T, BS, TRANS> &ring, float *tile
                 next(item);
             }
         }
+        if constexpr (Rg::HALF && !EXACT) {
+            if (__builtin_expect(any_nan(acc), 0)) {
+                again |= 1u << u;
+                continue;
+            }
+        }
         // every input of the block has been read: the results take their places
         if (l16 < G::TV) {
 #pragma unroll
@@ -226,6 +285,11 @@ __device__ __forceinline__ void stage_from(Ring<T, BS, TRANS> &ring, float *tile
                 for (int r = 0; r < 4; ++r) e[(16 * rt + 4 * kg + r) * SK] = acc[rt][r];
         }
     }
+    if constexpr (Rg::HALF && !EXACT)
+        for (; __builtin_expect(again != 0, 0); again &= again - 1) {
+            const int blk = wave * G::NBW + __builtin_ctz(again), ln = fresh(lane);
+            plain_where_nan<BS, SK>(tile + (ln & 15 & (G::TV - 1)) * G::ROWP + at(blk), W, blk, ln);
+        }
 }
 
 template <typename T, int BS, int SK, bool TRANS = false, typename At>
@@ -286,12 +350,15 @@ __global__ __launch_bounds__(Geo<BS>::THREADS, 4) void matmul_kernel(const T *__
     }
 }
 
-// NT row tiles of one block from row row0 on, the block's inputs at e (stride SK), the matrices in registers: the products
-// of stage_from, in its order
+// NT row tiles of block blk of W from row row0 on (all of them, or with EXACT a part), the block's inputs at e (stride SK), the
+// matrices in registers: the products of stage_from, in its order
 template <typename T, int BS, int SK, bool EXACT, int NT>
-__device__ __forceinline__ void block_products(float *e, const f32x4 (&w)[NT][Ring<T, BS>::WV], int row0, int l16, int kg)
+__device__ __forceinline__ void block_products(float *e, const f32x4 (&w)[NT][Ring<T, BS>::WV], const T *__restrict__ W, int blk,
+                                               int row0, int lane)
 {
     typedef Geo<BS> G;
+    static_assert(EXACT || NT == G::RT, "");
+    const int l16 = lane & 15, kg = lane >> 4;
     f32x4 acc[NT];
     if constexpr (Ring<T, BS>::HALF) {
         constexpr int CH = BS / 32, PARTS = EXACT ? 1 : 3;
@@ -325,6 +392,12 @@ __device__ __forceinline__ void block_products(float *e, const f32x4 (&w)[NT][Ri
             for (int j = 0; j < G::Q; ++j) acc[rt] = mfma(w[rt][j >> 2][j & 3], bv[j], acc[rt]);
         }
     }
+    if constexpr (Ring<T, BS>::HALF && !EXACT) {
+        if (__builtin_expect(any_nan(acc), 0)) {
+            plain_where_nan<BS, SK>(e, W, blk, lane);
+            return;
+        }
+    }
     if (l16 < G::TV) {
 #pragma unroll
         for (int rt = 0; rt < NT; ++rt)
@@ -348,7 +421,7 @@ __global__ __launch_bounds__(Geo<BS>::THREADS, Geo<BS>::THREADS / 256) void matm
     constexpr int NB = 16 / G::WAVES;                        // blocks of L of a wave
     constexpr bool EARLY = BS == 32 || Rg::HALF;             // registers for both matrices
     extern __shared__ __attribute__((aligned(16))) float tile[];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15, kg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15;
     const int part = blockIdx.x % G::RT;
     const int64_t v0 = (int64_t)(blockIdx.x / G::RT) * G::TV;
     f32x4 wr[G::NBW][1][Rg::WV], wl[NB][G::RT][Rg::WV];
@@ -371,11 +444,17 @@ __global__ __launch_bounds__(Geo<BS>::THREADS, Geo<BS>::THREADS / 256) void matm
     __syncthreads();
     float *mine = tile + (l16 & (G::TV - 1)) * G::ROWP;
 #pragma unroll
-    for (int u = 0; u < G::NBW; ++u) block_products<T, BS, G::SH, true, 1>(mine + wave * G::NBW + u, wr[u], 16 * part, l16, kg);
+    for (int u = 0; u < G::NBW; ++u) {
+        const int blk = wave * G::NBW + u;
+        block_products<T, BS, G::SH, true, 1>(mine + blk, wr[u], R, blk, 16 * part, lane);
+    }
     if constexpr (!EARLY) request_l();
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < NB; ++u) block_products<T, BS, 1, false, G::RT>(mine + (16 * part + wave * NB + u) * G::SH, wl[u], 0, l16, kg);
+    for (int u = 0; u < NB; ++u) {
+        const int blk = 16 * part + wave * NB + u;
+        block_products<T, BS, 1, false, G::RT>(mine + blk * G::SH, wl[u], L, blk, 0, lane);
+    }
     __syncthreads();
     for (int piece = threadIdx.x; piece < G::TV * BS * 4; piece += G::THREADS) {   // four r of one s
         const int v = piece / (BS * 4), s = piece / 4 % BS, r = 16 * part + 4 * (piece % 4);
@@ -607,6 +686,45 @@ __device__ __forceinline__ void preload_t(TRing<T> &ring, const T *__restrict__ 
     for (int d = 0; d < TRing<T>::DEPTH; ++d) request_t<T>(W, wave * Geo<32>::NBW + d, lane, ring.w[d]);
 }
 
+// A block's two operands of row tiles 0 and 1 from its requested pairs
+__device__ __forceinline__ void transposed_operands(const uint32_t (&w)[8], h16::op8 (&a)[2])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        a[0][j] = __builtin_amdgcn_perm(w[2 * j + 1], w[2 * j], 0x05040100u);
+        a[1][j] = __builtin_amdgcn_perm(w[2 * j + 1], w[2 * j], 0x07060302u);
+    }
+}
+
+// plain_where_nan for a transposed block
+template <int SK>
+__device__ __forceinline__ void plain_where_nan_t(float *e, const bf16_t *__restrict__ W, int blk, int lane)
+{
+    const int kg = lane >> 4;
+    uint32_t w[8];
+    request_t<bf16_t>(W, blk, lane, w);
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = e[(8 * kg + j) * SK];
+    h16::op8 b[3], a[2];
+    split3(x, b);
+    transposed_operands(w, a);
+    f32x4 acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}}, plain[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
+    for (int part = 2; part >= 0; --part)
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) acc[rt] = h16::mfma<bf16_t>(a[rt], b[part], acc[rt]);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        plain[0] = mfma(h16::lo32<bf16_t>(w[j]), x[j], plain[0]);
+        plain[1] = mfma(h16::hi32<bf16_t>(w[j]), x[j], plain[1]);
+    }
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) e[(8 * kg + 2 * r + rt) * SK] = acc[rt][r] != acc[rt][r] ? plain[rt][r] : acc[rt][r];
+}
+
 // One transposed factor in place, its first blocks in the ring.
 template <typename T, int SK, typename At>
 __device__ __forceinline__ void stage_t(TRing<T> &ring, float *tile, const T *__restrict__ W, int wave, int lane, At at)
@@ -615,6 +733,7 @@ __device__ __forceinline__ void stage_t(TRing<T> &ring, float *tile, const T *__
     constexpr int DEPTH = TRing<T>::DEPTH;
     const int l16 = lane & 15, kg = lane >> 4;
     float *mine = tile + l16 * G::ROWP;
+    uint32_t again = 0;   // as in stage_from
 #pragma unroll
     for (int u = 0; u < G::NBW; ++u) {
         float *e = mine + at(wave * G::NBW + u);
@@ -626,11 +745,7 @@ __device__ __forceinline__ void stage_t(TRing<T> &ring, float *tile, const T *__
         if constexpr (sizeof(T) == 2) {
             h16::op8 b[3], a[2];
             split3(x, b);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                a[0][j] = __builtin_amdgcn_perm(w[2 * j + 1], w[2 * j], 0x05040100u);
-                a[1][j] = __builtin_amdgcn_perm(w[2 * j + 1], w[2 * j], 0x07060302u);
-            }
+            transposed_operands(w, a);
 #pragma unroll
             for (int part = 2; part >= 0; --part)
 #pragma unroll
@@ -647,20 +762,23 @@ __device__ __forceinline__ void stage_t(TRing<T> &ring, float *tile, const T *__
             asm volatile("" : "+s"(src) : "v"(acc[1][0]));   // (the request stays behind these products)
             request_t<T>(src, wave * G::NBW + u + DEPTH, lane, ring.w[u % DEPTH]);
         }
+        if constexpr (sizeof(T) == 2) {
+            if (__builtin_expect(any_nan(acc), 0)) {
+                again |= 1u << u;
+                continue;
+            }
+        }
         // every input of the block has been read: the results take their places
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) e[(8 * kg + 2 * r + rt) * SK] = acc[rt][r];
     }
-}
-
-// The same value, unknown to the compiler: addresses derived from it are formed at their use instead of being kept in
-// registers over a persistent workgroup's tiles (with the sums there is no room for them: 556 bytes of spills a lane).
-__device__ __forceinline__ int fresh(int v)
-{
-    asm volatile("" : "+v"(v));
-    return v;
+    if constexpr (sizeof(T) == 2)
+        for (; __builtin_expect(again != 0, 0); again &= again - 1) {
+            const int blk = wave * G::NBW + __builtin_ctz(again), ln = fresh(lane);
+            plain_where_nan_t<SK>(tile + (ln & 15) * G::ROWP + at(blk), W, blk, ln);
+        }
 }
 
 // A thread's share of a 16 x 1024 tile: piece p holds elements i .. i + 3 of row v(p).

@@ -163,3 +163,21 @@ def test_bf16_parts_of_wide_and_non_finite_values(mm, b, batch):
     assert torch.equal(got[torch.isinf(got)].sign(), want[torch.isinf(want)].sign())
     for r in range(2, batch):   # the result's rounding to bf16 (2^-9) is the only one that shows
         assert rel_l2(got[r].numpy(), want[r].numpy()) <= 2.0 ** -8
+
+
+# The same with an infinite weight.  Every entry is +-1/2 or +-1, so that all sums are exact in fp32 as in fp64, most values
+# have no more bits than bf16 (their lower parts are zero), and a sum is zero exactly where plain floating point has it zero
+# and makes a NaN of it; few rows, and as many as take the kernel for many
+@pytest.mark.parametrize("factor", ["R", "L"])
+@pytest.mark.parametrize("b,batch", [(32, 21), (32, 2064), (64, 11), (64, 520)])
+def test_infinite_bf16_weights(mm, b, batch, factor):
+    announce("matmul infinite weight", b, batch, factor)
+    g = torch.Generator().manual_seed(b + batch)
+    x, R, L = (torch.tensor([-1.0, -0.5, 0.5, 1.0])[torch.randint(4, shape, generator=g)] for shape in ((batch, b * b), (b, b, b), (b, b, b)))
+    {"R": R, "L": L}[factor][3, 18, 5] = float("inf")
+    got = mm.monarch_matmul(x.bfloat16().cuda(), R.bfloat16().cuda(), L.bfloat16().cuda()).cpu()
+    z = torch.einsum("krc,xck->xrk", R.double(), x.double().reshape(batch, b, b))
+    want = torch.einsum("jlc,xjc->xlj", L.double(), z).reshape(batch, b * b)
+    assert torch.isinf(want).any()
+    assert torch.equal(torch.nan_to_num(got, nan=0.25, posinf=3e38, neginf=-3e38), torch.nan_to_num(want.bfloat16(), nan=0.25, posinf=3e38, neginf=-3e38))
+    assert torch.equal(torch.isnan(got), torch.isnan(want))

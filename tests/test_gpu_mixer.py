@@ -125,3 +125,33 @@ def test_empty_batch(mm):
     w = workloads.mixer_inputs(1, 4, 16, seed=0)
     w["u"] = w["u"][:0]; w["g_in"] = w["g_in"][:0]; w["g_out"] = w["g_out"][:0]
     assert _run(mm, w).shape == (0, 4, 256)
+
+
+# An infinite entry in each of the four matrices, bf16 blocks of 32 and 64.  Every other entry is 1/2 or 1, of the rows +-1/2 or
+# +-1: what the factors multiply is exact in fp32 as in fp64 and often has no more bits than bf16 (its lower parts are zero);
+# infinities, their signs and NaN must be where plain floating point has them
+@pytest.mark.parametrize("gates", [False, True])
+@pytest.mark.parametrize("factor", ["R1", "L1", "R2", "L2"])
+@pytest.mark.parametrize("b", [32, 64])
+def test_infinite_bf16_weights(mm, b, factor, gates):
+    announce("mixer infinite weight", b, factor, gates)
+    g = torch.Generator().manual_seed(b)
+    few = lambda *shape: torch.tensor([-1.0, -0.5, 0.5, 1.0])[torch.randint(4, shape, generator=g)]     # noqa: E731
+    B, H = 3, 7
+    u, K, g_in, g_out = few(B, H, b * b), few(H, b * b).abs(), few(B, H, b * b), few(B, H, b * b)
+    m = {name: few(b, b, b).abs() for name in ("R1", "L1", "R2", "L2")}
+    m[factor][3, 18, 5] = float("inf")
+    if not gates:
+        g_in = g_out = None
+    put = lambda t: None if t is None else t.bfloat16().cuda()      # noqa: E731
+    got = mm.monarch_mixer(put(u), put(K), put(g_in), put(g_out), *(put(m[name]) for name in ("R1", "L1", "R2", "L2"))).cpu()
+
+    def product(x, R, L):
+        z = torch.einsum("krc,xck->xrk", R.double(), x.reshape(-1, b, b))
+        return torch.einsum("jlc,xjc->xlj", L.double(), z).reshape(B, H, b * b)
+    want = product(K.double() * product((u * g_in if gates else u).double(), m["R1"], m["L1"]), m["R2"], m["L2"])
+    want = want * g_out.double() if gates else want
+    assert torch.isinf(want).any()
+    # finite values: the rounding of the result to bf16, and of the last stage's sums (b terms of fp32)
+    largest = want[torch.isfinite(want)].abs().max() if torch.isfinite(want).any() else 0.0
+    torch.testing.assert_close(got.double(), want, rtol=2.0 ** -8, atol=float(largest) * b * 2.0 ** -24, equal_nan=True)

@@ -130,3 +130,26 @@ def test_blocks_of_32_one_output_alone(mm, asked):
                                     5, 7, 32, mm.F32, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
     assert rc == 0, lib.monarch_last_error()
     assert rel_l2(host(out), want) <= TOL_F32
+
+
+# An infinite entry in each matrix, bf16 blocks of 32: every other entry is +-1/2 or +-1, so that all sums are exact and most
+# values have no lower bf16 parts.  The transposed stages of dx; 16 rows: none repeated in a tile
+@pytest.mark.parametrize("factor", ["R", "L"])
+def test_infinite_bf16_weights_in_the_product_gradient(mm, factor):
+    announce("matmul backward infinite weight", factor)
+    b, batch = 32, 16
+    g = torch.Generator().manual_seed(5)
+    x, dy, R, L = (torch.tensor([-1.0, -0.5, 0.5, 1.0])[torch.randint(4, shape, generator=g)]
+                   for shape in ((batch, b * b), (batch, b * b), (b, b, b), (b, b, b)))
+    {"R": R, "L": L}[factor][3, 18, 5] = float("inf")
+    got = mm.monarch_matmul_backward(*(t.bfloat16().cuda() for t in (x, R, L, dy)))
+    mid = torch.einsum("krc,xck->xrk", R.double(), x.double().reshape(batch, b, b))
+    d = dy.double().reshape(batch, b, b)      # [s][r]
+    dmid = torch.einsum("jlc,xlj->xjc", L.double(), d)
+    want = {"dx": torch.einsum("krc,xrk->xck", R.double(), dmid).reshape(batch, b * b),
+            "dR": torch.einsum("xrk,xck->krc", dmid, x.double().reshape(batch, b, b)), "dL": torch.einsum("xlj,xjc->jlc", d, mid)}
+    assert torch.isinf(want["dx"]).any()
+    for name, t in zip(("dx", "dR", "dL"), got):
+        w = want[name].to(t.dtype)
+        assert torch.equal(torch.isnan(t.cpu()), torch.isnan(w)), name
+        assert torch.equal(torch.nan_to_num(t.cpu(), nan=0.25, posinf=3e38, neginf=-3e38), torch.nan_to_num(w, nan=0.25, posinf=3e38, neginf=-3e38)), name
