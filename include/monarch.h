@@ -167,13 +167,14 @@ size_t monarch_mixer_workspace_bytes(int64_t B, int H, int bs, monarch_dtype dt)
 /*
  * Gradients of monarch_mixer (Sec. 3.2 Eq. 2, gated form; the chain rule through gate, M1, kernel product, M2,
  * gate), for a training step: with S = sum <dy, y>,
- *   du, dg_in, dg_out: (B, H, N), type dt;   dK: (H, N) float32 (a sum over the sequences);
+ *   du, dg_in, dg_out: (B, H, N), type dt;   dK: (H, N) float32 (a sum over the sequences, in a fixed order);
  *   dR1, dL1, dR2, dL2: [bs][bs][bs] float32 (sums over all rows, by floating-point atomic adds: the last bits depend
  *   on the order of the additions).  All are overwritten.  Any of them may be NULL (not computed); dg_in / dg_out
  *   need their gate.
- * Composed from the order-2 product and its gradient kernels with elementwise kernels between them; the
- * intermediate rows (type dt) travel through ws: monarch_mixer_backward_workspace_bytes(B, H, bs, dt) bytes of
- * device memory of the caller (five arrays of the size of u).
+ * ws: monarch_mixer_backward_workspace_bytes(B, H, bs, dt) bytes of device memory of the caller, five arrays of the size
+ * of u for every block size.  Blocks of 32: two kernels, of the intermediates only the gradient between the two matrices
+ * (type dt) and parts of dK pass through ws.  Other blocks: composed from the order-2 product and its gradient kernels
+ * with elementwise kernels between them, five arrays of intermediate rows (type dt) pass through ws.
  * Errors: EINVAL (null required pointer with B * H > 0, a gate's gradient without the gate, misalignment, overlap),
  * ESHAPE, EWORKSPACE, EDTYPE, EHIP.
  */

@@ -107,11 +107,11 @@ int launch_matmul_inplace(const void *x, const void *R, const void *L, void *y, 
 bool monarch_inplace_backward_supported(int bs, monarch_dtype dt);
 int launch_matmul_backward_inplace(const void *x, const void *R, const void *L, const void *dy, void *dx, float *dR, float *dL,
                                    int64_t batch, int bs, monarch_dtype dt, hipStream_t s);
-// Gradients of the mixer with blocks of 32 (csrc/monarch_inplace.hip): dK and the factor gradients added to cleared buffers,
-// ds: scratch of the size of u; any output may be null
+// Gradients of the mixer with blocks of 32 (csrc/monarch_inplace.hip): the factor gradients added to cleared buffers;
+// scratch: mixer_backward_workspace_bytes; any output may be null
 bool mixer_backward_inplace_takes(int64_t B, int bs, monarch_dtype dt);
 int launch_mixer_backward_inplace(const void *u, const void *K, const void *g_in, const void *g_out, const void *R1, const void *L1,
-                                  const void *R2, const void *L2, const void *dy, void *ds, void *du, float *dK, void *dg_in,
+                                  const void *R2, const void *L2, const void *dy, void *scratch, void *du, float *dK, void *dg_in,
                                   void *dg_out, float *dR1, float *dL1, float *dR2, float *dL2, int64_t B, int H, monarch_dtype dt,
                                   hipStream_t s);
 // sequence mixer with two general square order-2 Monarch matrices (csrc/mixer.hip); g_in, g_out may be null

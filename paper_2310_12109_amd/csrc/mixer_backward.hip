@@ -6,7 +6,8 @@
 //   dg_out = dy o w         dw = dy o g_out     (dt, dR2, dL2) = grad of M2 at (t, dw)
 //   dK[h] = sum_b dt o s    ds = dt o K         (da, dR1, dL1) = grad of M1 at (a, ds)
 //   du = da o g_in          dg_in = da o u
-// Blocks of 32 take two kernels instead (csrc/monarch_inplace), which keep everything but ds in LDS and registers.
+// Blocks of 32 take two kernels instead (csrc/monarch_inplace), which keep everything but ds (and the parts of dK that
+// workgroups share) in LDS and registers.
 #include "kernels.h"
 
 namespace monarch {
@@ -101,17 +102,17 @@ __global__ void clear_kernel(float *p, size_t n)
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0.0f;
 }
 
-// the sums of a call, whole pieces of four floats each; any may be null
+// the factor gradients of a call, n floats each, a multiple of four; any may be null
 struct SumBuffers {
-    float *p[5];
-    size_t n[5];
+    float *p[4];
+    size_t n;
 };
 __global__ void clear_sums_kernel(SumBuffers b)
 {
     const size_t stride = (size_t)gridDim.x * blockDim.x, first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int q = 0; q < 5; ++q)
+    for (int q = 0; q < 4; ++q)
         if (b.p[q])
-            for (size_t i = first; i < b.n[q] / 4; i += stride) reinterpret_cast<f32x4 *>(b.p[q])[i] = f32x4{0, 0, 0, 0};
+            for (size_t i = first; i < b.n / 4; i += stride) reinterpret_cast<f32x4 *>(b.p[q])[i] = f32x4{0, 0, 0, 0};
 }
 
 static unsigned blocks_for(size_t n)
@@ -202,9 +203,8 @@ int launch_mixer_backward(const void *u, const void *K, const void *g_in, const 
                           monarch_dtype dt, void *ws, hipStream_t s)
 {
     if (mixer_backward_inplace_takes(B, bs, dt)) {
-        const size_t w = (size_t)bs * bs * bs;
-        const mixb::SumBuffers sums = {{dK, dR1, dL1, dR2, dL2}, {(size_t)H * bs * bs, w, w, w, w}};
-        if (dK || dR1 || dL1 || dR2 || dL2) hipLaunchKernelGGL(mixb::clear_sums_kernel, dim3(256), dim3(256), 0, s, sums);
+        const mixb::SumBuffers sums = {{dR1, dL1, dR2, dL2}, (size_t)bs * bs * bs};
+        if (dR1 || dL1 || dR2 || dL2) hipLaunchKernelGGL(mixb::clear_sums_kernel, dim3(256), dim3(256), 0, s, sums);
         MONARCH_HIP_CHECK(hipGetLastError());
         return launch_mixer_backward_inplace(u, K, g_in, g_out, R1, L1, R2, L2, dy, ws, du, dK, dg_in, dg_out, dR1, dL1, dR2, dL2, B, H, dt, s);
     }

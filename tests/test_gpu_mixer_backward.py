@@ -116,6 +116,24 @@ def test_blocks_of_32_channel_by_channel(mm, B, H, gates, bf16):
     _check(mm, w, _dy(w, 6, bf16), TOL_BF16 if bf16 else TOL_F32, bf16=bf16)
 
 
+# dK is a sum over the sequences in a fixed order, also where workgroups share a channel: parts of it at the ends of two runs of
+# tiles, and of whole runs (one channel, many tiles).  The same bits from every call, and a one in each row counted once
+@pytest.mark.parametrize("B,H,bf16", [(40, 128, False), (40, 128, True), (20000, 1, False), (4100, 3, True), (1, 600, False)])
+def test_blocks_of_32_kernel_gradient_repeats(mm, B, H, bf16):
+    announce("mixer backward b=32, dK again and again", B, H, bf16)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    normal = lambda *shape: torch.randn(*shape, device="cuda", generator=gen)     # noqa: E731
+    u, dy, K = normal(B, H, 1024).to(dt), normal(B, H, 1024).to(dt), normal(H, 1024).to(dt)
+    m = [(normal(32, 32, 32) * 32 ** -0.5).to(dt) for _ in range(4)]
+    first = mm.monarch_mixer_backward(u, K, None, None, *m, dy)["dK"]
+    for _ in range(12):
+        assert torch.equal(mm.monarch_mixer_backward(u, K, None, None, *m, dy)["dK"], first)
+    one = torch.eye(32, device="cuda").expand(32, 32, 32).contiguous().to(dt)     # all blocks the identity: y = K o u up to the order
+    got = mm.monarch_mixer_backward(torch.ones_like(u), K, None, None, one, one, one, one, torch.ones_like(u))["dK"]
+    assert torch.equal(got, torch.full_like(got, float(B)))
+
+
 @pytest.mark.parametrize("asked", GRADS)
 def test_blocks_of_32_one_output_alone(mm, asked):
     announce("mixer backward b=32, one output:", asked)
