@@ -314,6 +314,11 @@ size_t monarch_fft_workspace_bytes(int64_t rows, int N, const int *factors, int 
  *               (klen <= nfft); this is the bidirectional kernel of M2-BERT.
  * u, y, g_in, g_out: (B,H,n); k: (H,klen); all of type dt.  g_in and/or g_out
  * may be NULL (no gate).
+ * Rows share transforms where every factor is 16, 32, 64 or 128: two batch
+ * entries (2p, 2p+1) of a channel, or at B = 1 two neighbouring channels, may
+ * be one complex row.  An infinity or NaN in one of them is then in both
+ * results, and the rounding error of both is that of the larger.  With any
+ * other factor every row is transformed by itself.
  * Errors: EINVAL, ESHAPE (as monarch_fft; n > nfft; aliasing sizes), EDTYPE,
  * EWORKSPACE, EHIP.
  */

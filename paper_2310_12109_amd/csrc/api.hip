@@ -965,8 +965,13 @@ static int conv_run(const void *u, const void *k, const void *g_in, const void *
     if (fused == 1) return launch_conv_mfma_2048(u, k, g_in, g_out, y, B, H, n, klen, dt, s);
     if (fused == 2) return launch_conv_mfma_256(u, k, g_in, g_out, y, B, H, n, klen, s);
     if (fused == 3) return launch_conv_mfma_16k(u, k, g_in, g_out, y, B, H, n, klen, s);
-    if (conv_f32_fft_supported(nfft, dt))   // any split of nfft into factors is the same transform
-        return launch_conv_f32_fft(u, k, g_in, g_out, y, B, H, n, klen, nfft, s);
+    if (conv_f32_fft_supported(nfft, dt)) {
+        // Any split of nfft into factors is the same transform.  The passes of the matrix-core splits share a complex row between
+        // two rows (an infinity of one is in the other, and the rounding of a large one), those of the others never did:
+        // there a caller finds the entries of a batch apart, and pays for it with twice the transforms.
+        const int per = fft_mfma_f32_supported(nfft, factors, nf, dt) ? 2 : 1;
+        return launch_conv_f32_fft(u, k, g_in, g_out, y, B, H, n, klen, nfft, per, s);
+    }
 
     const size_t buf = align_up(rows * nfft * sizeof(float2), 256);
     void *bufs[2] = {ws, (char *)ws + buf};

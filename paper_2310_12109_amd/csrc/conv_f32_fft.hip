@@ -1,7 +1,7 @@
 // Fused gated convolution in fp32 for transform lengths 256 .. 8192 (powers of two), on the vector unit:
 //   y = g_out o (F^-1 (F k' o F (g_in o u)'))[0 : n]
-// Two rows of a channel (batch entries 2 p, 2 p + 1) are one complex row z = x0 + i x1 (the kernel is real); a slot of
-// N / A threads holds it in registers, A values per thread, from the loads to the stores.  The Monarch factors of
+// Two rows of a channel (batch entries 2 p, 2 p + 1) are one complex row z = x0 + i x1 (the kernel is real), or one row
+// fills both parts (per = 1); a slot of N / A threads holds it in registers, A values per thread, from the loads to the stores.  The Monarch factors of
 // the transform are A, 16 and R (N = A 16 R): with t the thread, t = t2 + R j2,
 //   over j  (n = t + 16 R j):  X1[k1][t]      times w_N^(t k1)
 //   over j2:                   X2[k1][k2][t2] times w_(16 R)^(t2 k2)
@@ -135,7 +135,7 @@ template <int L, bool LOW = false> __device__ __forceinline__ void dft(float2 (&
 template <int A, int R, bool HALF, bool GIN, bool GOUT>
 __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_kernel(
     const float *__restrict__ u, const float *__restrict__ k, const float *__restrict__ g_in, const float *__restrict__ g_out,
-    float *__restrict__ y, int B, int H, int n, int klen, int splits, int items)
+    float *__restrict__ y, int B, int H, int n, int klen, int per, int splits, int items)
 {
     typedef Geo<A, R> G;
     constexpr int M = G::M, T = G::T, U = G::U, P = G::P, Q = G::Q, JN = HALF ? A / 2 : A, PR = 16 / R;
@@ -146,7 +146,7 @@ __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_
     const int64_t item = (int64_t)blockIdx.x * G::SLOTS + slot;
     const bool live_item = item < items;
     const int h = live_item ? (int)(item % H) : 0, split = live_item ? (int)(item / H) : 0;
-    const int pairs = (B + 1) / 2;
+    const int pairs = per == 2 ? (B + 1) / 2 : B;   // complex rows of a channel
     __syncthreads();
 
     // forward transform of v (value n = t + M j in v[j]) into z[unit][m R + k3].  It begins by storing to every k1 row of the
@@ -247,8 +247,8 @@ __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_
         if constexpr (G::SLOTS == 1) {
             if (!live) break;
         }
-        const int b0 = live ? 2 * p : 0;
-        const bool two = b0 + 1 < B;
+        const int b0 = live ? per * p : 0;
+        const bool two = per == 2 && b0 + 1 < B;
         const int64_t r0 = ((int64_t)b0 * H + h) * n, r1 = two ? r0 + (int64_t)H * n : r0;
         // (requested here and not a pair ahead: the 32 more registers spill at three workgroups per compute unit, 34 -> 43 us)
 #pragma unroll
@@ -285,12 +285,12 @@ __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_
 
 template <int A, int R>
 static int launch(const float *u, const float *k, const float *g_in, const float *g_out, float *y, int B, int H, int n, int klen,
-                  hipStream_t s)
+                  int per, hipStream_t s)
 {
     typedef Geo<A, R> G;
     // a slot transforms its channel's kernel once and then takes the pairs split, split + splits, ...: as many splits of a
     // channel's pairs as give every compute unit its three workgroups
-    const int pairs = (B + 1) / 2;
+    const int pairs = per == 2 ? (B + 1) / 2 : B;
     int64_t splits = ((int64_t)768 * G::SLOTS + H - 1) / H;
     if (splits > pairs) splits = pairs;
     const int64_t items = splits * H;
@@ -302,7 +302,7 @@ static int launch(const float *u, const float *k, const float *g_in, const float
         auto kern = conv_kernel<A, R, HALF, GI, GO>;                                                                            \
         if (G::LDS_BYTES > 65536)                                                                                               \
             MONARCH_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS_BYTES)); \
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(G::THREADS), G::LDS_BYTES, s, u, k, g_in, g_out, y, B, H, n, klen, (int)splits, (int)items); \
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(G::THREADS), G::LDS_BYTES, s, u, k, g_in, g_out, y, B, H, n, klen, per, (int)splits, (int)items); \
     } while (0)
     switch ((half ? 4 : 0) | (g_in ? 2 : 0) | (g_out ? 1 : 0)) {
     case 7: MONARCH_CFFT(true, true, true); break;
@@ -327,17 +327,17 @@ bool conv_f32_fft_supported(int nfft, monarch_dtype dt)
 }
 
 int launch_conv_f32_fft(const void *u, const void *k, const void *g_in, const void *g_out, void *y, int B, int H, int n, int klen,
-                        int nfft, hipStream_t s)
+                        int nfft, int per, hipStream_t s)
 {
     const float *uf = (const float *)u, *kf = (const float *)k, *gi = (const float *)g_in, *go = (const float *)g_out;
     float *yf = (float *)y;
     switch (nfft) {
-    case 256: return cfft::launch<16, 1>(uf, kf, gi, go, yf, B, H, n, klen, s);
-    case 512: return cfft::launch<16, 2>(uf, kf, gi, go, yf, B, H, n, klen, s);
-    case 1024: return cfft::launch<16, 4>(uf, kf, gi, go, yf, B, H, n, klen, s);
-    case 2048: return cfft::launch<16, 8>(uf, kf, gi, go, yf, B, H, n, klen, s);
-    case 4096: return cfft::launch<16, 16>(uf, kf, gi, go, yf, B, H, n, klen, s);
-    default: return cfft::launch<32, 16>(uf, kf, gi, go, yf, B, H, n, klen, s);
+    case 256: return cfft::launch<16, 1>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
+    case 512: return cfft::launch<16, 2>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
+    case 1024: return cfft::launch<16, 4>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
+    case 2048: return cfft::launch<16, 8>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
+    case 4096: return cfft::launch<16, 16>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
+    default: return cfft::launch<32, 16>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
     }
 }
 

@@ -308,3 +308,22 @@ def test_fp32_short_rows_behind_the_kernel_spectrum(mm, factors, n, klen):
         pair = np.hypot(rows[b], rows[min(b ^ 1, 4)])
         assert (np.linalg.norm(first[b] - want[b], axis=1) <= 1e-6 * gain * pair).all(), b
     assert np.array_equal(first, _run(mm, w, factors, False, False))
+
+
+# Splits of a length that no matrix-core pass takes keep the entries of a batch apart: a row beside one with an infinity, a NaN
+# or values of 1e15 is what it is beside itself
+@pytest.mark.parametrize("factors", [(8, 64), (8, 8, 16), (256, 8), (4, 1024), (2048, 4)])
+def test_fp32_other_splits_keep_rows_apart(mm, factors):
+    announce("conv fp32 rows apart", factors)
+    nfft = int(np.prod(factors))
+    n = nfft // 2 - 3
+    w = workloads.conv_inputs(5, 6, n, seed=n, gates="normal")
+    w["u"][1] = w["u"][0]
+    w["g_in"][1], w["g_out"][1] = w["g_in"][0], w["g_out"][0]
+    alone = _run(mm, {k: v if k == "k" else np.ascontiguousarray(v[:1]) for k, v in w.items()}, factors, False)
+    assert rel_l2(alone, _oracle(w, nfft)[:1]) <= TOL_F32
+    for strange in (np.inf, np.nan, 1e15):
+        w["u"][1, :, n // 2] = strange
+        y = _run(mm, w, factors, False)
+        assert np.array_equal(y[:1], alone), strange
+        assert np.isfinite(y[2:]).all()
