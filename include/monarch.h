@@ -236,7 +236,10 @@ size_t monarch_hyena_layer_workspace_bytes(int B, int n, int d, int klen, int nf
  *   O[j]     = sum_i X1~[i] o XV[i][j]                  multiplied by X1~ position by position
  * Projections, short convolutions and the output projection as in monarch_hyena_layer, which is this entry point at
  * head_dim = 1.  The products X2~[i] o V~[j] and their convolutions go through the workspace as tensors of
- * head_dim times the activation size each (rounded to dt there); the sum over i is formed in fp32.
+ * head_dim times the activation size each (rounded to dt there); the sum over i is formed in fp32.  Without wrap-around
+ * and for heads of 5 to 16 features the sum over i may be taken first instead (where that is faster):
+ *   O[j][t] = sum_s V~[j][s] (k_long[head][t-s] S[s][t]),   S[s][t] = sum_i X2~[i][s] X1~[i][t],
+ * S in fp32, its product with k_long rounded to dt once, no tensor of head_dim times the activation size.
  * 1 <= head_dim <= 64, head_dim divides d.  ws: monarch_hyena_heads_layer_workspace_bytes.
  * Errors: as monarch_hyena_layer; ESHAPE for a head dimension that is out of range or does not divide d.
  */

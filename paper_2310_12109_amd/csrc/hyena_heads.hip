@@ -244,18 +244,25 @@ static int run(const void *proj, void *x12v, void *o, const void *k_short, const
 
 }  // namespace hheads
 
-// The work is n^2 per head here and d_h^2 transforms there.  Whole layer, us, convolutions against this kernel (B n = 8192
-// at bf16, 2048 at fp32, d = 768 or 640):
-//              d_h = 16                     d_h = 8                      d_h = 5
-//   n      bf16         fp32          bf16         fp32          bf16         fp32
-//   128    367 : 140    527 : 128     228 : 153    292 : 117     141 : 129    193 : 115
-//   1024   281 : 124    415 : 169     178 : 146    286 : 202     140 : 159    177 : 173
-//   2048   478 : 163    672 : 217     293 : 179    426 : 259     204 : 213    264 : 250
-// so from 8 features on every length the kernel takes, from 5 on up to n = 512 (bf16 204 : 138, fp32 202 : 139).  With
-// 4 features (rows padded to 4) an earlier form gained nothing at n = 128 and lost from n = 1024 on (147 : 280).
-bool hyena_heads_supported(int B, int n, int d, int klen, int nfft, int head_dim)
+// The work is n^2 per head here and d_h^2 transforms there.  Whole layer, us, convolutions against this kernel, d = 768 (640 at
+// d_h = 5), B n = 8192:
+//   bf16   d_h = 16       8            6            5            fp32   d_h = 16       12           8            6
+//   n =  128   327 : 134    220 : 154    197 : 165    144 : 135      745 :  391    648 : 407    555 : 429    508 : 459
+//        512   532 : 114    312 : 129    256 : 151    197 : 143      771 :  405    666 : 429    560 : 472    509 : 528
+//       1024   279 : 120    184 : 140    164 : 169    132 : 152      772 :  444    667 : 476    559 : 548    506 : 638
+//       2048   477 : 139    305 : 173    253 : 198    191 : 185      767 :  525    662 : 581    557 : 726    501 : 864
+//       4096   578 : 178    348 : 236    291 : 280    223 : 262     1080 :  806    905 : 914    744 : 1183   663 : 1438
+//       8192  1348 : 253    441 : 362    309 : 439    237 : 419     3792 : 1135   2954 : 1336  2106 : 1864  1686 : 2379
+// bf16, and fp32 beyond the convolution kernel of one launch (n = 8192; n = 4200, d_h = 8, d = 256 1125 : 362; splits whose rows it
+// takes one by one): from 8 features on always, from 5 on up to n = 512.  fp32 within that kernel: n < 2 d_h^3, which
+// parts the table and what lies between (d_h = 10: n = 1024 684 : 521, 2048 663 : 653; 7: 512 591 : 515; 6: 256 518 : 475;
+// 5: 128 111 : 109, 256 377 : 377); at B = 1 the line lies a little lower (8: 1024 111 : 128, 12: 2048 187 : 205).  With
+// 4 features (rows padded to 4) an earlier form gained nothing at n = 128 and lost from n = 1024 on (bf16 147 : 280).
+bool hyena_heads_supported(int B, int n, int d, int klen, int nfft, const int *factors, int nf, int head_dim, monarch_dtype dt)
 {
-    if (head_dim < 8 && n > 512) return false;
+    if (conv_f32_fft_supported(nfft, dt) && fft_mfma_f32_supported(nfft, factors, nf, dt)) {
+        if (n >= 2 * head_dim * head_dim * head_dim) return false;
+    } else if (head_dim < 8 && n > 512) return false;
     if (head_dim < hheads::MIN_DH || head_dim > hheads::ROW || n < 8 || n % 8 || n > 8192) return false;
     if ((int64_t)n + klen - 1 > nfft) return false;   // a circular convolution that wraps
     return (int64_t)B * (d / head_dim) <= 65535 && (int64_t)B * ((n + hheads::TU - 1) / hheads::TU) <= 4 * 65535;

@@ -250,7 +250,7 @@ static int run(const void *u, const void *W_in, const void *b_in, const void *k_
     // 2. short depthwise convolutions (with the projection bias)
     // (the scratch of the calls without it is more than enough but for rows of a few positions of small heads)
     const size_t heads_ws = align_up(3 * plane * es, 256) + align_up(plane * es, 256) + hyena_heads_bytes(B, n, d, dh, dt);
-    const bool paired = hyena_heads_supported(B, n, d, klen, nfft, dh) &&
+    const bool paired = hyena_heads_supported(B, n, d, klen, nfft, factors, nf, dh, dt) &&
                         heads_ws <= hyena_layer_workspace_bytes(B, n, d, klen, nfft, factors, nf, dh, dt);
     if (paired) {   // and 3. for heads of few features: every pair of positions instead of d_h^2 convolutions
         o = shrt;

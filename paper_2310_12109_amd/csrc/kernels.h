@@ -95,7 +95,7 @@ int launch_hyena_layer(const void *u, const void *W_in, const void *b_in, const 
                        int causal, int head_dim, monarch_dtype dt, void *ws, size_t ws_bytes, hipStream_t s);
 // the short convolutions and the head part of that layer as two products per pair of positions, 5 <= d_h <= 16, no
 // circular wrap (csrc/hyena_heads.hip): proj (B, 3, d, n) -> o (B, d, n); x12v: hyena_heads_bytes of scratch
-bool hyena_heads_supported(int B, int n, int d, int klen, int nfft, int head_dim);
+bool hyena_heads_supported(int B, int n, int d, int klen, int nfft, const int *factors, int nf, int head_dim, monarch_dtype dt);
 size_t hyena_heads_bytes(int B, int n, int d, int head_dim, monarch_dtype dt);
 int launch_hyena_heads(const void *proj, void *x12v, void *o, const void *k_short, const void *b_in, const void *k_long, int B, int d,
                        int n, int taps, int klen, int dh, monarch_dtype dt, hipStream_t s);

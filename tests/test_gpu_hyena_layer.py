@@ -125,11 +125,14 @@ def test_heads_argument_checks(mm):
 
 
 # the pairs kernel: steps of 32 and units of 64 positions with remainders, one position piece, kernels shorter than a unit,
-# every padding of the features (5 .. 16), batches that leave waves of a workgroup idle; fp32 and bf16
+# every padding of the features (5 .. 16), batches that leave waves of a workgroup idle, the longest sums it takes; fp32 and
+# bf16 (fp32 takes the convolutions at n = 512 with 6 features and at n = 2048 with 8)
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("B,n,d,dh,klen,factors", [(1, 8, 16, 16, 8, (16, 16)), (3, 40, 45, 9, 40, (16, 16)), (5, 72, 10, 5, 7, (16, 16)),
                                                    (2, 512, 36, 6, 512, (64, 32)), (1, 1032, 48, 16, 1, (64, 64)),
-                                                   (2, 1032, 24, 12, 1000, (64, 64)), (1, 2048, 32, 8, 2048, (64, 64))])
+                                                   (2, 1032, 24, 12, 1000, (64, 64)), (1, 2048, 32, 8, 2048, (64, 64)),
+                                                   (1, 4096, 16, 16, 4096, (128, 64)), (1, 4104, 8, 8, 4104, (128, 128)),
+                                                   (1, 8192, 8, 8, 8192, (128, 128))])
 def test_heads_pairs(mm, B, n, d, dh, klen, factors, bf16):
     announce("hyena layer heads by pairs", B, n, d, dh, klen, factors, bf16)
     w = workloads.hyena_layer_inputs(B, n, d, ks=3, klen=klen, seed=n + d + dh, bf16=bf16, head_dim=dh)
