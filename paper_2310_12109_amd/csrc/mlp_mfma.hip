@@ -890,6 +890,9 @@ namespace {
 // pays where the weights are large against a L2 of 4 MB: 768 -> 3072 in 4 blocks (2.4 MB), us, tiles first against blocks first:
 // 700 tokens 18.8 : 17.3, 4096 20.4 : 19.7, 16384 74.7 : 72.4; 1536 -> 6144 in 8 (4.7 MB): 1000 tokens 19.4 : 17.8.  512 -> 2048
 // in 8 (0.5 MB) is as fast either way, 1024 -> 4096 in 16 (1 MB) slower (9.8 : 10.1).  Grids of up to 65535 tiles.
+// Order 2 (three launches): the streamed kernel as fast either way (768: 16384 tokens 154.6 : 155.5, 32768 280 : 280, 65536
+// 558.6 : 552.7; 1536: 10922 tokens 232.0 : 231.1, 16384 288 : 288), so that it has one rule for both orders; the 64-token kernel
+// slower, because the launch before it left a tile's tokens in the L2 of its XCD (768: 4096 tokens 48.6 : 50.3).
 bool mlp_by_block(int d, int dh_blk, int64_t tiles) { return (int64_t)4 * d * dh_blk >= 2 << 20 && tiles <= 65535; }
 
 template <typename E>
@@ -987,7 +990,6 @@ int launch_typed(const void *x, void *y, int64_t tokens, int d, int d_hidden, in
     }
     const size_t split_lds = mlp1::split_lds_bytes(din / 32, dh_blk);
     if (split_lds <= 160 * 1024) {
-        // (order 2: the launch before left a tile's tokens in the L2 of its XCD, 45.6 against 47.9 us at 4096 tokens of 768)
         const int by_block = !b1_interleaved && mlp_by_block(d, dh_blk, tiles);
         const dim3 pgrid = by_block ? dim3((unsigned)nb, (unsigned)tiles) : grid;
 #define MONARCH_LAUNCH_SPL(KSV, ACTV)                                                                            \

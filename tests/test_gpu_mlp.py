@@ -98,14 +98,15 @@ def test_streamed_weight_kernel_bf16(mm, order, tokens, d, dh, nb, act):
 
 
 # weights of more than 2 MB: workgroups in the order of the blocks.  One tile and a ragged last one of the 64-token kernel,
-# a block count that does not divide the eight XCDs, the 128-token kernel with a last tile of one token
-@pytest.mark.parametrize("tokens,d,dh,nb", [(1, 1536, 6144, 8), (70, 768, 3072, 4), (129, 960, 5760, 5), (16385, 768, 3072, 4)])
-def test_large_weights_block_by_block(mm, tokens, d, dh, nb):
-    announce("mlp block by block", tokens, d, dh, nb)
-    w = workloads.mlp_inputs(tokens, d, dh, nb, 1, seed=tokens, bf16=True, std=0.08)
-    y = _run(mm, w, nb, 1, 2, dh, True)
+# a block count that does not divide the eight XCDs, the 128-token kernel with a last tile of one token (there order 2 as well)
+@pytest.mark.parametrize("order,tokens,d,dh,nb", [(1, 1, 1536, 6144, 8), (1, 70, 768, 3072, 4), (1, 129, 960, 5760, 5),
+                                                  (1, 16385, 768, 3072, 4), (2, 16385, 768, 3072, 4)])
+def test_large_weights_block_by_block(mm, order, tokens, d, dh, nb):
+    announce("mlp block by block", order, tokens, d, dh, nb)
+    w = workloads.mlp_inputs(tokens, d, dh, nb, order, seed=tokens, bf16=True, std=0.08)
+    y = _run(mm, w, nb, order, 2, dh, True)
     rows = np.unique(np.r_[0, tokens - 1, np.random.default_rng(4).integers(0, tokens, 60)])
-    want = _oracle(w, nb, 1, 2, rows)
+    want = _oracle(w, nb, order, 2, rows)
     assert rel_l2(y[rows], want) <= TOL_BF16
     assert (np.linalg.norm(y[rows] - want, axis=1) / np.linalg.norm(want, axis=1)).max() <= 2.5 * TOL_BF16
 
