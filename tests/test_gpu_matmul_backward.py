@@ -133,6 +133,26 @@ def test_blocks_of_32_partial_outputs(mm):
     assert rel_l2(host(again[1]), wdR) <= TOL_F32 and rel_l2(host(again[2]), wdL) <= TOL_F32 and rel_l2(host(again[0]), wdx) <= TOL_F32
 
 
+# one gradient alone has an instance of its own, two or three share one: one tile with a single row, a ragged one, several tiles
+# per workgroup.  dx is the same sum in each (the same bits), dR and dL by atomic adds.
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("batch", [1, 37, 4100])
+def test_blocks_of_32_every_set_of_gradients(mm, batch, bf16):
+    announce("matmul backward b=32 sets of gradients", batch, bf16)
+    w = workloads.monarch_matmul_inputs(batch=batch, b=32, seed=batch + 40, bf16=bf16)
+    x, R, L, g = dev(w["x"], bf16), dev(w["R"], bf16), dev(w["L"], bf16), dev(_dy(batch, 1024, batch + 41, bf16=bf16), bf16)
+    full = [host(t) for t in mm.monarch_matmul_backward(x, R, L, g)]
+    for asked in range(1, 7):
+        need = [bool(asked >> i & 1) for i in range(3)]
+        got = mm.monarch_matmul_backward(x, R, L, g, *need)
+        assert [t is not None for t in got] == need
+        if need[0]:
+            assert np.array_equal(host(got[0]), full[0])
+        for i in (1, 2):
+            if need[i]:
+                assert rel_l2(host(got[i]), full[i]) <= TOL_F32
+
+
 def test_bf16_inputs(mm):
     announce("matmul backward bf16")
     w = workloads.monarch_matmul_inputs(batch=130, b=16, seed=3, bf16=True)
