@@ -490,16 +490,19 @@ __global__ __launch_bounds__(256, 1) void mlp_order1_stream_kernel(
     // therefore sits in LDS in fetch order, and lane (l16, kg) reads entry 4 l16 + kg of it (free of bank
     // conflicts, as measured).
     const int frow = lane >> 2, fkg = lane & 3;
-    int src_off[KS], src_step[KS];   // element offset of this lane's pieces in chunk 0, and per chunk
+    // this lane's pieces in chunk 0, and the elements from chunk to chunk.  (Pointers: the two matrices are allocations of their
+    // own, and the distance between them fits no 32-bit offset from one of them.)
+    const E *src[KS];
+    int src_step[KS];
 #pragma unroll
     for (int u = 0; u < KS; ++u) {
         const int o = wave + 4 * u;
         if (o < 2 * KS) {
             const int mt = o / KS, ks = o - mt * KS;
-            src_off[u] = (8 * (frow >> 2) + 4 * mt + (frow & 3)) * DIN + 32 * ks + 8 * fkg;
+            src[u] = W1b + (8 * (frow >> 2) + 4 * mt + (frow & 3)) * DIN + 32 * ks + 8 * fkg;
             src_step[u] = 32 * DIN;
         } else {
-            src_off[u] = (int)((W2b - W1b) + (16 * (o - 2 * KS) + frow) * dh + 8 * fkg);
+            src[u] = W2b + (16 * (o - 2 * KS) + frow) * dh + 8 * fkg;
             src_step[u] = 32;
         }
     }
@@ -507,7 +510,7 @@ __global__ __launch_bounds__(256, 1) void mlp_order1_stream_kernel(
         const int jj = j < nch ? j : nch - 1;
         uint4 *slot = lds_ring + (size_t)(j % ring) * OPS * 64;
 #pragma unroll
-        for (int u = 0; u < KS; ++u) dma_16(W1b + src_off[u] + jj * src_step[u], slot + (wave + 4 * u) * 64);
+        for (int u = 0; u < KS; ++u) dma_16(src[u] + jj * src_step[u], slot + (wave + 4 * u) * 64);
     };
     for (int a = 0; a < ring - 1; ++a) request(a);
 

@@ -111,6 +111,24 @@ def test_large_weights_block_by_block(mm, order, tokens, d, dh, nb):
     assert (np.linalg.norm(y[rows] - want, axis=1) / np.linalg.norm(want, axis=1)).max() <= 2.5 * TOL_BF16
 
 
+# the streamed kernel reads both matrices by one rule: they may lie more than 2^31 elements apart, in either order
+@pytest.mark.parametrize("first", ["W1_R", "W2_R"])
+def test_weights_far_apart(mm, first):
+    announce("mlp weights far apart", first)
+    w = workloads.mlp_inputs(16390, 768, 3072, 4, 1, seed=12, bf16=True, std=0.08)
+    t = {k: dev(v, True) for k, v in w.items()}
+    args = (t["b2"], 4, 1, 2, 3072)
+    near = mm.monarch_mlp(t["x"], t["W1_R"], None, t["b1"], t["W2_R"], None, *args)
+    n = t["W1_R"].numel()
+    room = torch.empty(2 ** 31 + 2 * n, dtype=torch.bfloat16, device="cuda")
+    ends = {first: room[:n], ("W2_R" if first == "W1_R" else "W1_R"): room[-n:]}
+    for k, v in ends.items():
+        v.copy_(t[k].reshape(-1))
+    far = mm.monarch_mlp(t["x"], ends["W1_R"].view_as(t["W1_R"]), None, t["b1"], ends["W2_R"].view_as(t["W2_R"]), None, *args)
+    torch.cuda.synchronize()
+    assert torch.equal(near, far)
+
+
 def test_no_bias_and_single_block(mm):
     announce("mlp nb=1 no bias")
     w = workloads.mlp_inputs(10, 16, 64, 1, 1, seed=3, bf16=False, std=0.3, bias=False)
