@@ -4,7 +4,8 @@
 // through registers.  The loads are written as assembly (M0 carries the LDS base and is saved / restored) so that
 // the compiler does not put its own wait-for-everything in front of every later LDS read: a kernel that uses
 // them waits by count (loads of all kinds share one in-order counter) and, if other waves read the data,
-// publishes it with a barrier itself.
+// publishes it with a barrier itself.  Between a scalar write of M0 and a direct-to-LDS load this family of chips asks for one
+// wait state, which the compiler inserts in its own code and which assembly has to bring along (s_nop).
 #pragma once
 
 #include <stdint.h>
@@ -19,7 +20,7 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) { return (uint32_
 __device__ __forceinline__ void dma_16_at(const void *src, uint32_t lds_addr)   // lds_addr wave-uniform
 {
     uint32_t saved_m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
                  : "=&s"(saved_m0)
                  : "s"(lds_addr), "v"(src)
                  : "memory");
@@ -32,8 +33,8 @@ __device__ __forceinline__ void dma_16(const void *src, void *lds_piece)
 __device__ __forceinline__ void dma_16_pair(const void *src0, const void *src1, uint32_t lds_first)
 {
     uint32_t saved_m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %2, off\n\t"
-                 "s_add_u32 m0, m0, 0x400\n\tglobal_load_lds_dwordx4 %3, off\n\ts_mov_b32 m0, %0"
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\t"
+                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, off\n\ts_mov_b32 m0, %0"
                  : "=&s"(saved_m0)
                  : "s"(lds_first), "v"(src0), "v"(src1)
                  : "memory", "scc");
