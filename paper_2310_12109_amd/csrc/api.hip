@@ -716,7 +716,7 @@ size_t monarch_causal_conv_workspace_bytes(int B, int H, int n, int klen, int nf
 {
     if (B <= 0 || H <= 0 || nfft <= 0) return 0;
     if (conv_fused_path(n, klen, factors, nf, dt)) return 0;   // fused kernels keep everything on chip
-    // The fp32 kernel of csrc/conv_f32_fft.hip does too, but only this shape was ever reported as needing nothing: the
+    // The fp32 kernel of csrc/conv_fft.hip does too, but only this shape was ever reported as needing nothing: the
     // other sizes stay as callers know them, and the calls that they refuse (a small workspace, the static entry) too.
     if (dt == MONARCH_F32 && factors && nf == 2 && factors[0] == 64 && factors[1] == 32 && n >= 1 && klen >= 1 && n <= 1024 &&
         klen <= 1024 && n % 4 == 0 && klen % 4 == 0)
@@ -728,7 +728,7 @@ size_t monarch_causal_conv_workspace_bytes(int B, int H, int n, int klen, int nf
 }
 
 // Convolution with the last two factors of every transform done in one kernel on LDS-resident chunks (bf16).
-// Two factors: three launches (spectrum of k, spectrum of the paired rows, inverse), no strided pass.
+// Two factors: two launches (spectrum of k; the rows, which stay on chip), no strided pass.
 // Three factors: the first factor is a strided pass before the chunk kernel (forward) and after it (inverse,
 // whose factors run in the opposite order), six launches; four when the rows pair two channels (one sequence per
 // channel): then one kernel does every chunk stage.  Spectra stay in the order the forward leaves them in.
@@ -744,8 +744,13 @@ static int conv_chunks_lds(const void *u, const void *k, const void *g_in, const
                            void *const bufs[2], float2 *kf, hipStream_t s)
 {
     // rows that share a complex row: two batch entries of a channel, or (one sequence per channel) two
-    // neighbouring channels, then with the kernels paired alike and separated again before the inverse
-    const bool by_channel = B == 1 && H >= 2;
+    // neighbouring channels, then with the kernels paired alike and separated again before the inverse.  With two factors
+    // that costs a launch and the rows between them, so channels stay alone (4096: H = 768 21 : 30 us, 3072 53 : 57; 8192: H = 256
+    // 20 : 40, 768 44 : 53, 1536 77 : 79) but where the workgroups, one per compute unit from 8192 on, have many rounds
+    // of rows to go, which pairs halve (8192: H = 1024 55 : 53, 3072 142 : 121; 16384: H = 1024 110 : 107, 1536 158 : 173, 3072 317 : 300).
+    const int rounds = (H + 255) / 256;
+    const bool pairs_pay = nf == 3 || (nfft >= 8192 && n % 8 == 0 && (rounds == 4 || rounds > 6));
+    const bool by_channel = pairs_pay && B == 1 && H >= 2;
     const bool paired = B >= 2 || by_channel;
     const int pair_stride = by_channel ? 1 : H;
     const int64_t crows = by_channel ? (H + 1) / 2 : paired ? (int64_t)((B + 1) / 2) * H : (int64_t)B * H;
@@ -770,8 +775,7 @@ static int conv_chunks_lds(const void *u, const void *k, const void *g_in, const
         first.real_rows = (int64_t)B * H;
     }
     int rc;
-    // two factors, rows of a multiple of 8 elements, kernels not paired: the rows never leave the chip
-    const bool one_kernel = nf == 2 && !by_channel && n % 8 == 0;
+    const bool one_kernel = nf == 2 && !by_channel;   // the rows never leave the chip
     // three factors, channels paired: four launches, the spectra never leave the chip
     const bool fused_middle = nf == 3 && by_channel && conv3_middle_supported(O, f1, f2, MONARCH_BF16);
     for (int which = 0; which < (one_kernel ? 1 : 2); ++which) {   // 0: spectrum of k (into kf), 1: spectrum of g_in o u (into bufs[1])
@@ -940,6 +944,24 @@ static int conv_passes_mfma(const void *u, const void *k, const void *g_in, cons
     return MONARCH_OK;
 }
 
+// bf16, nfft <= 8192, no MFMA kernel of one launch: the chunk kernels (two launches, matrix cores, the spectrum of k through
+// memory) or the kernel of csrc/conv_fft.hip (one launch, vector unit, every slot forms the spectrum of k).  us, the latter
+// first, c complex rows; `half`: n and klen at most nfft / 2, so that half of the vector unit's loads and stores do not exist:
+//   nfft      c = 64     512        768        1536        3072        12288
+//   1024     14 : 18   14 : 17    14 : 17    15 : 17    19 : 19     56 :  50   (not half 22 : 19 at 3072; n odd 18 : 22, 56 : 59)
+//   2048     14 : 17   14 : 17    16 : 19    24 : 25    37 : 37    109 : 109   (not half; n odd 105 : 127)
+//   4096     14 : 17   18 : 17    21 : 21    35 : 29    62 : 45                (half)
+//   4096     14 : 17   24 : 17    31 : 22    47 : 29    82 : 46                (not half; c = 256 15 : 17)
+//   8192     21 : 20   60 : 29   104 : 47   174 : 71   313 : 116               (32 values of a row per thread)
+static bool conv_chunks_faster(int B, int H, int n, int klen, int nfft)
+{
+    const int64_t c = ((int64_t)B + 1) / 2 * H;
+    const bool half = n <= nfft / 2 && klen <= nfft / 2;
+    if (nfft == 1024) return c >= 3072 && n % 8 == 0;
+    if (nfft == 4096) return c >= (half ? 1024 : 512);
+    return nfft == 8192;
+}
+
 static int conv_run(const void *u, const void *k, const void *g_in, const void *g_out, void *y,
                     int B, int H, int n, int klen, int nfft, const int *factors, int nf,
                     int causal, monarch_dtype dt, void *ws, size_t ws_bytes, monarch_stream_t stream)
@@ -961,17 +983,25 @@ static int conv_run(const void *u, const void *k, const void *g_in, const void *
         return fail(MONARCH_EWORKSPACE, "workspace of %zu bytes needed, %zu given", need, ws ? ws_bytes : (size_t)0);
     hipStream_t s = (hipStream_t)stream;
 
+    // Any split of nfft into factors is the same transform.  The matrix-core splits share a complex row between two rows (an
+    // infinity of one is in the other, and the rounding of a large one), the others never did: there a caller finds the
+    // entries of a batch apart, and pays for it with twice the transforms.
+    const bool mfma_split = fft_mfma_supported(nfft, factors, nf, dt);
+    const int per = mfma_split || fft_mfma_f32_supported(nfft, factors, nf, dt) ? 2 : 1;
+    static const int two_factors[][2] = {{16, 16}, {32, 32}, {64, 32}, {64, 64}, {128, 64}, {128, 128}};
+    if (mfma_split && !conv_fused_path(n, klen, factors, nf, dt))   // bf16: the split that the kernels of one or two launches are built for
+        for (const auto &f : two_factors)
+            if (f[0] * f[1] == nfft) {
+                factors = f;
+                nf = 2;
+            }
+
     const int fused = conv_fused_path(n, klen, factors, nf, dt);
     if (fused == 1) return launch_conv_mfma_2048(u, k, g_in, g_out, y, B, H, n, klen, dt, s);
     if (fused == 2) return launch_conv_mfma_256(u, k, g_in, g_out, y, B, H, n, klen, s);
     if (fused == 3) return launch_conv_mfma_16k(u, k, g_in, g_out, y, B, H, n, klen, s);
-    if (conv_f32_fft_supported(nfft, dt)) {
-        // Any split of nfft into factors is the same transform.  The passes of the matrix-core splits share a complex row between
-        // two rows (an infinity of one is in the other, and the rounding of a large one), those of the others never did:
-        // there a caller finds the entries of a batch apart, and pays for it with twice the transforms.
-        const int per = fft_mfma_f32_supported(nfft, factors, nf, dt) ? 2 : 1;
-        return launch_conv_f32_fft(u, k, g_in, g_out, y, B, H, n, klen, nfft, per, s);
-    }
+    if (conv_fft_supported(nfft) && !(mfma_split && conv_chunks_faster(B, H, n, klen, nfft)))
+        return launch_conv_fft(u, k, g_in, g_out, y, B, H, n, klen, nfft, per, dt, s);
 
     const size_t buf = align_up(rows * nfft * sizeof(float2), 256);
     void *bufs[2] = {ws, (char *)ws + buf};

@@ -1,4 +1,5 @@
-// Fused gated convolution in fp32 for transform lengths 256 .. 8192 (powers of two), on the vector unit:
+// Fused gated convolution, fp32 arithmetic on tensors of any element type, for transform lengths 256 .. 8192 (powers of two),
+// on the vector unit:
 //   y = g_out o (F^-1 (F k' o F (g_in o u)'))[0 : n]
 // Two rows of a channel (batch entries 2 p, 2 p + 1) are one complex row z = x0 + i x1 (the kernel is real), or one row
 // fills both parts (per = 1); a slot of N / A threads holds it in registers, A values per thread, from the loads to the stores.  The Monarch factors of
@@ -15,7 +16,9 @@
 // after the kernel's spectrum, whose transform leaves the waves at work on their rows of LDS.
 // B = 7, H = 384, n = 2004, N = 4096, both gates: 34 us (six MFMA passes through memory: 171), of it 17 us the rows at
 // the rate of a copy and about as much vector instructions (1300 per thread and pair, 3 waves per SIMD); the two
-// overlap only between workgroups.  B = 8, H = 768, n = 1024, N = 2048: 36 us (a 64 x 32 MFMA kernel: 75).  Three
+// overlap only between workgroups.  B = 8, H = 768, n = 1024, N = 2048: 36 us (a 64 x 32 MFMA kernel: 75).  16-bit tensors,
+// where no MFMA kernel of one launch takes the call: bf16, B = 37, H = 384, n = 136, N = 512: 21 us (passes through memory: 47); B = 8, H = 768, n = 1015, N = 2048: 34 (three chunk launches: 46);
+// fp16, B = 8, H = 768, n = 1016, a circular kernel, N = 2048: 51 (shape-generic passes: 2307).  Three
 // waves per SIMD: with 128 registers (four) the twiddles held in registers spill, 34 -> 47 us.  N = 8192 takes 32
 // values per thread and one wave per SIMD: 84 us at B = 2, H = 768, n = 4096 (passes: 293), 98 with two waves and spills.
 #include "const_roots.h"
@@ -132,10 +135,10 @@ template <int L, bool LOW = false> __device__ __forceinline__ void dft(float2 (&
 }
 
 // HALF: n <= N / 2 and klen <= N / 2 (zero padding): the upper half of the loads and of the outputs does not exist.
-template <int A, int R, bool HALF, bool GIN, bool GOUT>
+template <typename E, int A, int R, bool HALF, bool GIN, bool GOUT>
 __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_kernel(
-    const float *__restrict__ u, const float *__restrict__ k, const float *__restrict__ g_in, const float *__restrict__ g_out,
-    float *__restrict__ y, int B, int H, int n, int klen, int per, int splits, int items)
+    const E *__restrict__ u, const E *__restrict__ k, const E *__restrict__ g_in, const E *__restrict__ g_out,
+    E *__restrict__ y, int B, int H, int n, int klen, int per, int splits, int items)
 {
     typedef Geo<A, R> G;
     constexpr int M = G::M, T = G::T, U = G::U, P = G::P, Q = G::Q, JN = HALF ? A / 2 : A, PR = 16 / R;
@@ -233,7 +236,7 @@ __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_
 #pragma unroll
     for (int j = 0; j < A; ++j) {
         const int i = t + M * j;
-        v[j] = make_float2(j < JN && i < klen ? k[(int64_t)h * klen + i] : 0.0f, 0.0f);
+        v[j] = make_float2(j < JN && i < klen ? to_f32(k[(int64_t)h * klen + i]) : 0.0f, 0.0f);
     }
     forward(v, kf);
 #pragma unroll
@@ -256,8 +259,8 @@ __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_
             const int i = t + M * j;
             v[j] = make_float2(0.0f, 0.0f);
             if (j < JN && i < n) {
-                v[j] = make_float2(u[r0 + i], u[r1 + i]);
-                if (GIN) v[j] = make_float2(v[j].x * g_in[r0 + i], v[j].y * g_in[r1 + i]);
+                v[j] = make_float2(to_f32(u[r0 + i]), to_f32(u[r1 + i]));
+                if (GIN) v[j] = make_float2(v[j].x * to_f32(g_in[r0 + i]), v[j].y * to_f32(g_in[r1 + i]));
             }
         }
         float2 z[U][16];
@@ -275,16 +278,16 @@ __global__ __launch_bounds__((Geo<A, R>::THREADS), (A == 32 ? 1 : 3)) void conv_
             for (int j = 0; j < JN; ++j) {
                 const int i = t + M * j;
                 if (i < n) {
-                    y[r0 + i] = GOUT ? v[j].x * g_out[r0 + i] : v[j].x;
-                    if (two) y[r1 + i] = GOUT ? -v[j].y * g_out[r1 + i] : -v[j].y;
+                    y[r0 + i] = from_f32<E>(GOUT ? v[j].x * to_f32(g_out[r0 + i]) : v[j].x);
+                    if (two) y[r1 + i] = from_f32<E>(GOUT ? -v[j].y * to_f32(g_out[r1 + i]) : -v[j].y);
                 }
             }
         }
     }
 }
 
-template <int A, int R>
-static int launch(const float *u, const float *k, const float *g_in, const float *g_out, float *y, int B, int H, int n, int klen,
+template <typename E, int A, int R>
+static int launch(const E *u, const E *k, const E *g_in, const E *g_out, E *y, int B, int H, int n, int klen,
                   int per, hipStream_t s)
 {
     typedef Geo<A, R> G;
@@ -299,7 +302,7 @@ static int launch(const float *u, const float *k, const float *g_in, const float
     const bool half = n <= G::N / 2 && klen <= G::N / 2;
 #define MONARCH_CFFT(HALF, GI, GO)                                                                                              \
     do {                                                                                                                        \
-        auto kern = conv_kernel<A, R, HALF, GI, GO>;                                                                            \
+        auto kern = conv_kernel<E, A, R, HALF, GI, GO>;                                                                            \
         if (G::LDS_BYTES > 65536)                                                                                               \
             MONARCH_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS_BYTES)); \
         hipLaunchKernelGGL(kern, dim3(grid), dim3(G::THREADS), G::LDS_BYTES, s, u, k, g_in, g_out, y, B, H, n, klen, per, (int)splits, (int)items); \
@@ -321,24 +324,33 @@ static int launch(const float *u, const float *k, const float *g_in, const float
 
 }  // namespace cfft
 
-bool conv_f32_fft_supported(int nfft, monarch_dtype dt)
+bool conv_fft_supported(int nfft)
 {
-    return dt == MONARCH_F32 && nfft >= 256 && nfft <= 8192 && (nfft & (nfft - 1)) == 0;
+    return nfft >= 256 && nfft <= 8192 && (nfft & (nfft - 1)) == 0;
 }
 
-int launch_conv_f32_fft(const void *u, const void *k, const void *g_in, const void *g_out, void *y, int B, int H, int n, int klen,
-                        int nfft, int per, hipStream_t s)
+template <typename E>
+static int launch_conv_fft_as(const void *u, const void *k, const void *g_in, const void *g_out, void *y, int B, int H, int n, int klen,
+                              int nfft, int per, hipStream_t s)
 {
-    const float *uf = (const float *)u, *kf = (const float *)k, *gi = (const float *)g_in, *go = (const float *)g_out;
-    float *yf = (float *)y;
+    const E *ue = (const E *)u, *ke = (const E *)k, *gi = (const E *)g_in, *go = (const E *)g_out;
+    E *ye = (E *)y;
     switch (nfft) {
-    case 256: return cfft::launch<16, 1>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
-    case 512: return cfft::launch<16, 2>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
-    case 1024: return cfft::launch<16, 4>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
-    case 2048: return cfft::launch<16, 8>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
-    case 4096: return cfft::launch<16, 16>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
-    default: return cfft::launch<32, 16>(uf, kf, gi, go, yf, B, H, n, klen, per, s);
+    case 256: return cfft::launch<E, 16, 1>(ue, ke, gi, go, ye, B, H, n, klen, per, s);
+    case 512: return cfft::launch<E, 16, 2>(ue, ke, gi, go, ye, B, H, n, klen, per, s);
+    case 1024: return cfft::launch<E, 16, 4>(ue, ke, gi, go, ye, B, H, n, klen, per, s);
+    case 2048: return cfft::launch<E, 16, 8>(ue, ke, gi, go, ye, B, H, n, klen, per, s);
+    case 4096: return cfft::launch<E, 16, 16>(ue, ke, gi, go, ye, B, H, n, klen, per, s);
+    default: return cfft::launch<E, 32, 16>(ue, ke, gi, go, ye, B, H, n, klen, per, s);
     }
+}
+
+int launch_conv_fft(const void *u, const void *k, const void *g_in, const void *g_out, void *y, int B, int H, int n, int klen,
+                    int nfft, int per, monarch_dtype dt, hipStream_t s)
+{
+    if (dt == MONARCH_F32) return launch_conv_fft_as<float>(u, k, g_in, g_out, y, B, H, n, klen, nfft, per, s);
+    if (dt == MONARCH_BF16) return launch_conv_fft_as<bf16_t>(u, k, g_in, g_out, y, B, H, n, klen, nfft, per, s);
+    return launch_conv_fft_as<f16_t>(u, k, g_in, g_out, y, B, H, n, klen, nfft, per, s);
 }
 
 }  // namespace monarch

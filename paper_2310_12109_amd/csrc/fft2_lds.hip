@@ -282,7 +282,47 @@ __device__ __forceinline__ void unpack8(const u32x4 &w, float (&v)[8])
     }
 }
 
-// VEC: real rows are read and written 16 bytes (8 elements) at a time, which needs n_valid % 8 == 0; all
+// A piece of 8 neighbouring elements of a real row of n, elements e ... e + 7, e a multiple of 8.  Rows of any length but a multiple
+// of 8 start anywhere (PIECES == false): their pieces are unaligned 16-byte accesses.  The row's last piece is then loaded from
+// its last 8 elements, so that nothing past the tensor is touched, and shifted into place by piece_in_place, where the loads
+// have arrived; rows shorter than 8 are read element by element.  (Element by element for every row: 3.5 times as slow,
+// 271 -> 125 us for 6144 rows of 4087.)
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+template <bool PIECES> __device__ __forceinline__ u32x4 load_piece(const bf16_t *row, int e, int n)
+{
+    if constexpr (PIECES) return *reinterpret_cast<const u32x4 *>(row + (e < n ? e : 0));   // past the row: any valid address, the value is dropped
+    else if (n >= 8) return *reinterpret_cast<const u32x4_any *>(row + (e <= n - 8 ? e : n - 8));
+    u32x4 w = {0, 0, 0, 0};
+    const uint16_t *bits = reinterpret_cast<const uint16_t *>(row);
+#pragma unroll
+    for (int t = 0; t < 7; ++t)
+        if (t < n) w[t / 2] |= (uint32_t)bits[t] << (16 * (t & 1));
+    return w;
+}
+template <bool PIECES> __device__ __forceinline__ void piece_in_place(u32x4 &w, int e, int n)
+{
+    if constexpr (!PIECES) {
+        if (n >= 8 && e > n - 8 && e < n) {   // its first element is element n - 8 of the row: e - (n - 8) elements too low
+            const int sh = 16 * (e - (n - 8));
+            const uint64_t lo = (uint64_t)w[1] << 32 | w[0], hi = (uint64_t)w[3] << 32 | w[2];
+            const uint64_t l = sh >= 64 ? hi >> (sh - 64) : (lo >> sh) | (hi << 1) << (63 - sh), h = sh >= 64 ? 0 : hi >> sh;
+            w = u32x4{(uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32)};
+        }
+    }
+}
+template <bool PIECES> __device__ __forceinline__ void store_piece(bf16_t *row, int e, int n, u32x4 w)
+{
+    if constexpr (PIECES) __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(row + e));
+    else if (e + 8 <= n) *reinterpret_cast<u32x4_any *>(row + e) = w;
+    else {
+        uint16_t *bits = reinterpret_cast<uint16_t *>(row);
+#pragma unroll
+        for (int t = 0; t < 7; ++t)
+            if (e + t < n) bits[e + t] = (uint16_t)(w[t / 2] >> (16 * (t & 1)));
+    }
+}
+
+// VEC: real rows are read and written in aligned pieces, which needs n_valid % 8 == 0; all
 // global loads of a chunk are issued together, those of the next chunk (and the output gates of this one)
 // before the stages of the current one, so that they are in flight while the matrix cores work.
 // TWO (Hermitian separation, three factors): a workgroup takes a chunk o and its mirror chunk O - o in one turn,
@@ -348,24 +388,21 @@ __global__ __launch_bounds__(F1 >= 128 || F2 >= 128 ? 512 : 256) void fft2_lds_k
                 }
             }
         } else if constexpr (REAL_IN) {
-            if constexpr (VEC) {
-                const int64_t ra = LOAD == LD_REAL_PAIR ? pair_first_row(p, rc) : rc;
-                const bool hasb = LOAD == LD_REAL_PAIR && ra + p.pair_stride < p.real_rows;
-                const bf16_t *ua = (const bf16_t *)p.in + ra * p.n_valid, *ub = hasb ? ua + (int64_t)p.pair_stride * p.n_valid : ua;
-                const bf16_t *ga = p.gate ? (const bf16_t *)p.gate + ra * p.n_valid : ua;
-                const bf16_t *gb = p.gate && hasb ? ga + (int64_t)p.pair_stride * p.n_valid : ga;
+            const int64_t ra = LOAD == LD_REAL_PAIR ? pair_first_row(p, rc) : rc;
+            const bool hasb = LOAD == LD_REAL_PAIR && ra + p.pair_stride < p.real_rows;
+            const bf16_t *ua = (const bf16_t *)p.in + ra * p.n_valid, *ub = hasb ? ua + (int64_t)p.pair_stride * p.n_valid : ua;
+            const bf16_t *ga = p.gate ? (const bf16_t *)p.gate + ra * p.n_valid : ua;
+            const bf16_t *gb = p.gate && hasb ? ga + (int64_t)p.pair_stride * p.n_valid : ga;
 #pragma unroll
-                for (int it = 0; it < NIT8; ++it) {
-                    const int e = 8 * (tid + it * THREADS);
-                    const int ee = e < p.n_valid ? e : 0;   // past the row: any valid address, the value is dropped
-                    if (it * 8 * THREADS < lim) {
-                        // (ordinary loads: streaming ones made the forward transform 6 % slower, 27.7 -> 29.5 us at 6144 x 2048)
-                        za[it] = *reinterpret_cast<const u32x4 *>(ua + ee);
-                        zc[it] = *reinterpret_cast<const u32x4 *>(ga + ee);
-                        if (LOAD == LD_REAL_PAIR) {
-                            zb[it] = *reinterpret_cast<const u32x4 *>(ub + ee);
-                            zd[it] = *reinterpret_cast<const u32x4 *>(gb + ee);
-                        }
+            for (int it = 0; it < NIT8; ++it) {
+                const int e = 8 * (tid + it * THREADS);
+                if (it * 8 * THREADS < lim) {
+                    // (ordinary loads: streaming ones made the forward transform 6 % slower, 27.7 -> 29.5 us at 6144 x 2048)
+                    za[it] = load_piece<VEC>(ua, e, p.n_valid);
+                    zc[it] = load_piece<VEC>(ga, e, p.n_valid);
+                    if (LOAD == LD_REAL_PAIR) {
+                        zb[it] = load_piece<VEC>(ub, e, p.n_valid);
+                        zd[it] = load_piece<VEC>(gb, e, p.n_valid);
                     }
                 }
             }
@@ -429,56 +466,40 @@ __global__ __launch_bounds__(F1 >= 128 || F2 >= 128 ? 512 : 256) void fft2_lds_k
             const int64_t rc = q / p.O;
             const int64_t ra = LOAD == LD_REAL_PAIR ? pair_first_row(p, rc) : rc;
             const bool hasb = LOAD == LD_REAL_PAIR && ra + p.pair_stride < p.real_rows;
-            if constexpr (VEC) {
 #pragma unroll
-                for (int it = 0; it < NIT8; ++it) {
-                    const int e = 8 * (tid + it * THREADS);
-                    if (e < lim) {
-                        float a[8], b[8], g[8];
-                        const bool ok = e < p.n_valid;
-                        unpack8(za[it], a);
-                        if (p.gate) {
-                            unpack8(zc[it], g);
+            for (int it = 0; it < NIT8; ++it) {
+                const int e = 8 * (tid + it * THREADS);
+                if (e < lim) {
+                    float a[8], b[8], g[8];
+                    const bool ok = e < p.n_valid;
+                    piece_in_place<VEC>(za[it], e, p.n_valid);
+                    unpack8(za[it], a);
+                    if (p.gate) {
+                        piece_in_place<VEC>(zc[it], e, p.n_valid);
+                        unpack8(zc[it], g);
 #pragma unroll
-                            for (int t = 0; t < 8; ++t) a[t] *= g[t];
-                        }
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) b[t] = 0.0f;
-                        if (LOAD == LD_REAL_PAIR && hasb) {
-                            unpack8(zb[it], b);
-                            if (p.gate) {
-                                unpack8(zd[it], g);
-#pragma unroll
-                                for (int t = 0; t < 8; ++t) b[t] *= g[t];
-                            }
-                        }
-                        u32x4 w0, w1;
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            w0[t] = ok ? pack2(a[t], b[t]) : 0u;
-                            w1[t] = ok ? pack2(a[4 + t], b[4 + t]) : 0u;
-                        }
-                        *reinterpret_cast<u32x4 *>(tile + tix(e)) = w0;
-                        *reinterpret_cast<u32x4 *>(tile + tix(e + 4)) = w1;
+                        for (int t = 0; t < 8; ++t) a[t] *= g[t];
                     }
-                }
-            } else {   // any row length: element by element
-                const bf16_t *ua = (const bf16_t *)p.in + ra * p.n_valid, *ub = ua + (int64_t)p.pair_stride * p.n_valid;
-                const bf16_t *ga = p.gate ? (const bf16_t *)p.gate + ra * p.n_valid : nullptr;
-                const bf16_t *gb = ga ? ga + (int64_t)p.pair_stride * p.n_valid : nullptr;
-                for (int e = 4 * tid; e < lim; e += 4 * THREADS) {
-                    u32x4 w;
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) b[t] = 0.0f;
+                    if (LOAD == LD_REAL_PAIR && hasb) {
+                        piece_in_place<VEC>(zb[it], e, p.n_valid);
+                        unpack8(zb[it], b);
+                        if (p.gate) {
+                            piece_in_place<VEC>(zd[it], e, p.n_valid);
+                            unpack8(zd[it], g);
+#pragma unroll
+                            for (int t = 0; t < 8; ++t) b[t] *= g[t];
+                        }
+                    }
+                    u32x4 w0, w1;
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        const bool ok = e + t < p.n_valid;
-                        float re = ok ? (float)ua[e + t] : 0.0f, im = ok && hasb ? (float)ub[e + t] : 0.0f;
-                        if (ga) {
-                            re *= ok ? (float)ga[e + t] : 0.0f;
-                            im *= ok && hasb ? (float)gb[e + t] : 0.0f;
-                        }
-                        w[t] = pack2(re, im);
+                        w0[t] = ok ? pack2(a[t], b[t]) : 0u;
+                        w1[t] = ok ? pack2(a[4 + t], b[4 + t]) : 0u;
                     }
-                    *reinterpret_cast<u32x4 *>(tile + tix(e)) = w;
+                    *reinterpret_cast<u32x4 *>(tile + tix(e)) = w0;
+                    *reinterpret_cast<u32x4 *>(tile + tix(e + 4)) = w1;
                 }
             }
         } else {
@@ -562,7 +583,7 @@ __global__ __launch_bounds__(F1 >= 128 || F2 >= 128 ? 512 : 256) void fft2_lds_k
         const int64_t ra = STORE == ST_REAL_PAIR ? pair_first_row(p, rc) : rc;
         const bool hasb = STORE == ST_REAL_PAIR && ra + p.pair_stride < p.real_rows;
         const void *out_gate = FUSED ? p.gate_out : p.gate;
-        u32x4 oga[REAL_OUT && VEC ? NIT8 : 1], ogb[REAL_OUT && VEC ? NIT8 : 1], kfr[FUSED ? NIT4 : 1];
+        u32x4 oga[REAL_OUT ? NIT8 : 1], ogb[REAL_OUT ? NIT8 : 1], kfr[FUSED ? NIT4 : 1];
         if constexpr (FUSED) {   // this chunk's kernel spectrum, multiplied in between the two transforms
             const uint32_t *ksrc = (const uint32_t *)p.kf + (rc % p.H) * (int64_t)p.N;
 #pragma unroll
@@ -571,15 +592,15 @@ __global__ __launch_bounds__(F1 >= 128 || F2 >= 128 ? 512 : 256) void fft2_lds_k
                 if (e < CH) kfr[it] = *reinterpret_cast<const u32x4 *>(ksrc + e);
             }
         }
-        if constexpr (REAL_OUT && VEC) {
+        if constexpr (REAL_OUT) {
             if (out_gate) {
                 const bf16_t *ga = (const bf16_t *)out_gate + ra * p.n_valid, *gb = hasb ? ga + (int64_t)p.pair_stride * p.n_valid : ga;
 #pragma unroll
                 for (int it = 0; it < NIT8; ++it) {
                     const int e = 8 * (tid + it * THREADS);
                     if (e < p.n_valid) {
-                        oga[it] = *reinterpret_cast<const u32x4 *>(ga + e);
-                        if (STORE == ST_REAL_PAIR) ogb[it] = *reinterpret_cast<const u32x4 *>(gb + e);
+                        oga[it] = load_piece<VEC>(ga, e, p.n_valid);
+                        if (STORE == ST_REAL_PAIR) ogb[it] = load_piece<VEC>(gb, e, p.n_valid);
                     }
                 }
             }
@@ -668,56 +689,36 @@ __global__ __launch_bounds__(F1 >= 128 || F2 >= 128 ? 512 : 256) void fft2_lds_k
         } else {
             // F^-1 = conj(F conj(.)) / N: first member = Re / N, second = -Im / N, times the output gate
             bf16_t *ya = (bf16_t *)p.out + ra * p.n_valid, *yb = ya + (int64_t)p.pair_stride * p.n_valid;
-            if constexpr (VEC) {
 #pragma unroll
-                for (int it = 0; it < NIT8; ++it) {
-                    const int e = 8 * (tid + it * THREADS);
-                    if (e < p.n_valid) {
-                        const bool gated = out_gate != nullptr;
-                        const u32x4 w0 = *reinterpret_cast<const u32x4 *>(tile + tix(e));
-                        const u32x4 w1 = *reinterpret_cast<const u32x4 *>(tile + tix(e + 4));
-                        float va[8], vb[8], g[8];
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            va[t] = lo_f32(w0[t]) * p.scale;
-                            vb[t] = -hi_f32(w0[t]) * p.scale;
-                            va[4 + t] = lo_f32(w1[t]) * p.scale;
-                            vb[4 + t] = -hi_f32(w1[t]) * p.scale;
-                        }
-                        if (gated) {
-                            unpack8(oga[it], g);
-#pragma unroll
-                            for (int t = 0; t < 8; ++t) va[t] *= g[t];
-                        }
-                        __builtin_nontemporal_store(u32x4{pack2(va[0], va[1]), pack2(va[2], va[3]), pack2(va[4], va[5]), pack2(va[6], va[7])},
-                                                    reinterpret_cast<u32x4 *>(ya + e));
-                        if (STORE == ST_REAL_PAIR && hasb) {
-                            if (gated) {
-                                unpack8(ogb[it], g);
-#pragma unroll
-                                for (int t = 0; t < 8; ++t) vb[t] *= g[t];
-                            }
-                            __builtin_nontemporal_store(u32x4{pack2(vb[0], vb[1]), pack2(vb[2], vb[3]), pack2(vb[4], vb[5]), pack2(vb[6], vb[7])},
-                                                        reinterpret_cast<u32x4 *>(yb + e));
-                        }
-                    }
-                }
-            } else {
-                const bf16_t *ga = out_gate ? (const bf16_t *)out_gate + ra * p.n_valid : nullptr;
-                const bf16_t *gb = ga ? ga + (int64_t)p.pair_stride * p.n_valid : nullptr;
-                for (int e = 4 * tid; e < p.n_valid; e += 4 * THREADS) {
-                    const u32x4 w = *reinterpret_cast<const u32x4 *>(tile + tix(e));
+            for (int it = 0; it < NIT8; ++it) {
+                const int e = 8 * (tid + it * THREADS);
+                if (e < p.n_valid) {
+                    const bool gated = out_gate != nullptr;
+                    const u32x4 w0 = *reinterpret_cast<const u32x4 *>(tile + tix(e));
+                    const u32x4 w1 = *reinterpret_cast<const u32x4 *>(tile + tix(e + 4));
+                    float va[8], vb[8], g[8];
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        if (e + t < p.n_valid) {
-                            float va = lo_f32(w[t]) * p.scale, vb = -hi_f32(w[t]) * p.scale;
-                            if (ga) va *= (float)ga[e + t];
-                            ya[e + t] = (bf16_t)va;
-                            if (hasb) {
-                                if (gb) vb *= (float)gb[e + t];
-                                yb[e + t] = (bf16_t)vb;
-                            }
+                        va[t] = lo_f32(w0[t]) * p.scale;
+                        vb[t] = -hi_f32(w0[t]) * p.scale;
+                        va[4 + t] = lo_f32(w1[t]) * p.scale;
+                        vb[4 + t] = -hi_f32(w1[t]) * p.scale;
+                    }
+                    if (gated) {
+                        piece_in_place<VEC>(oga[it], e, p.n_valid);
+                        unpack8(oga[it], g);
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) va[t] *= g[t];
+                    }
+                    store_piece<VEC>(ya, e, p.n_valid, u32x4{pack2(va[0], va[1]), pack2(va[2], va[3]), pack2(va[4], va[5]), pack2(va[6], va[7])});
+                    if (STORE == ST_REAL_PAIR && hasb) {
+                        if (gated) {
+                            piece_in_place<VEC>(ogb[it], e, p.n_valid);
+                            unpack8(ogb[it], g);
+#pragma unroll
+                            for (int t = 0; t < 8; ++t) vb[t] *= g[t];
                         }
+                        store_piece<VEC>(yb, e, p.n_valid, u32x4{pack2(vb[0], vb[1]), pack2(vb[2], vb[3]), pack2(vb[4], vb[5]), pack2(vb[6], vb[7])});
                     }
                 }
             }
@@ -1036,9 +1037,8 @@ static int launch_modes(const Fft2Args &p, hipStream_t s)
     if (p.O == 1 && p.inverse && p.load == LD_C32_CONJ && p.store == ST_CPLX_CONJ_SCALE)   // monarch_ifft, complex bf16 rows
         return launch_one<F1, F2, true, LD_C32_CONJ, ST_CPLX_CONJ_SCALE>(p, s);
     if (!p.inverse && p.store != ST_C16) {   // whole convolution in one kernel
-        if (p.n_valid % 8) return fail(MONARCH_EINVAL, "internal: the fused chunk convolution needs rows of a multiple of 8 elements");
-        if (p.load == LD_REAL_PAIR && p.store == ST_REAL_PAIR) return launch_vec<F1, F2, false, LD_REAL_PAIR, ST_REAL_PAIR, true>(p, s);
-        if (p.load == LD_REAL && p.store == ST_REAL_SCALE_GATE) return launch_vec<F1, F2, false, LD_REAL, ST_REAL_SCALE_GATE, true>(p, s);
+        if (p.load == LD_REAL_PAIR && p.store == ST_REAL_PAIR) return launch_one<F1, F2, false, LD_REAL_PAIR, ST_REAL_PAIR>(p, s);
+        if (p.load == LD_REAL && p.store == ST_REAL_SCALE_GATE) return launch_one<F1, F2, false, LD_REAL, ST_REAL_SCALE_GATE>(p, s);
         return fail(MONARCH_EINVAL, "internal: fused chunk convolution modes %d/%d not built", p.load, p.store);
     }
     if (!p.inverse) {

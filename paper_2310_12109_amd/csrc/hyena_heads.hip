@@ -260,7 +260,7 @@ static int run(const void *proj, void *x12v, void *o, const void *k_short, const
 // 4 features (rows padded to 4) an earlier form gained nothing at n = 128 and lost from n = 1024 on (bf16 147 : 280).
 bool hyena_heads_supported(int B, int n, int d, int klen, int nfft, const int *factors, int nf, int head_dim, monarch_dtype dt)
 {
-    if (conv_f32_fft_supported(nfft, dt) && fft_mfma_f32_supported(nfft, factors, nf, dt)) {
+    if (conv_fft_supported(nfft) && fft_mfma_f32_supported(nfft, factors, nf, dt)) {
         if (n >= 2 * head_dim * head_dim * head_dim) return false;
     } else if (head_dim < 8 && n > 512) return false;
     if (head_dim < hheads::MIN_DH || head_dim > hheads::ROW || n < 8 || n % 8 || n > 8192) return false;

@@ -182,11 +182,11 @@ bool conv_mfma_16k_supported(int n, int klen, const int *factors, int nf, monarc
 int launch_conv_mfma_16k(const void *u, const void *k, const void *g_in, const void *g_out, void *y,
                          int B, int H, int n, int klen, hipStream_t s);
 
-// fp32, power-of-two lengths 256 .. 8192, any n and klen: the whole convolution of a complex row (per = 2: two batch entries of
-// a channel, 1: one) in registers, as a radix-16 FFT on the vector unit (csrc/conv_f32_fft.hip)
-bool conv_f32_fft_supported(int nfft, monarch_dtype dt);
-int launch_conv_f32_fft(const void *u, const void *k, const void *g_in, const void *g_out, void *y, int B, int H, int n, int klen,
-                        int nfft, int per, hipStream_t s);
+// fp32 arithmetic for any element type, power-of-two lengths 256 .. 8192, any n and klen: the whole convolution of a complex
+// row (per = 2: two batch entries of a channel, 1: one) in registers, as a radix-16 FFT on the vector unit (csrc/conv_fft.hip)
+bool conv_fft_supported(int nfft);
+int launch_conv_fft(const void *u, const void *k, const void *g_in, const void *g_out, void *y, int B, int H, int n, int klen,
+                    int nfft, int per, monarch_dtype dt, hipStream_t s);
 
 // nfft = 256 = 16 x 16, n <= 128, klen <= 256, bf16 I/O; no workspace.
 bool conv_mfma_256_supported(int n, int klen, const int *factors, int nf, monarch_dtype dt);

@@ -327,3 +327,53 @@ def test_fp32_other_splits_keep_rows_apart(mm, factors):
         y = _run(mm, w, factors, False)
         assert np.array_equal(y[:1], alone), strange
         assert np.isfinite(y[2:]).all()
+
+
+# 16-bit tensors on the vector unit's transform: every length, rows of any length, all gates, a circular kernel, an odd batch.
+# Inputs and products are fp32 there, so what is left is one rounding of the result: at most 2^-9 (bf16) or 2^-12 (fp16) of
+# every entry, beside 1e-6 of the transforms.  Splits that no matrix-core pass takes, and fp16, keep the rows apart.
+@pytest.mark.parametrize("B,H,n,klen,factors,gates,causal,dtype", [
+    (1, 3, 256, 256, (16, 16), "normal", False, torch.bfloat16),
+    (5, 9, 255, 200, (32, 16), "normal", True, torch.bfloat16),
+    (2, 5, 512, 512, (16, 32), "in", False, torch.bfloat16),
+    (3, 4, 503, 503, (32, 32), "out", True, torch.bfloat16),
+    (3, 3, 1015, 1015, (64, 32), "normal", True, torch.bfloat16),
+    (2, 3, 1016, 2048, (64, 32), "normal", False, torch.float16),
+    (3, 3, 1001, 77, (64, 32), "none", True, torch.float16),
+    (1, 4, 2047, 2047, (16, 16, 16), "normal", True, torch.bfloat16),
+    (2, 3, 2048, 4096, (4, 1024), "normal", False, torch.bfloat16),
+    (3, 2, 4095, 4095, (4, 2048), "normal", True, torch.float16),
+])
+def test_16_bit_rows_in_registers(mm, B, H, n, klen, factors, gates, causal, dtype):
+    announce("conv 16-bit rows in registers", B, H, n, klen, factors, gates, causal, dtype)
+    nfft = int(np.prod(factors))
+    w = workloads.conv_inputs(B, H, n, seed=n + klen, gates="none" if gates == "none" else "normal")
+    w["k"] = np.random.default_rng(klen).standard_normal((H, klen)).astype(np.float32) / np.sqrt(klen)
+    if gates in ("in", "out"):
+        w["g_out" if gates == "in" else "g_in"] = None
+    t = {name: None if v is None else torch.from_numpy(np.ascontiguousarray(v)).cuda().to(dtype) for name, v in w.items()}
+    w = {name: None if v is None else v.float().cpu().numpy() for name, v in t.items()}
+    y = host(mm.monarch_causal_conv(t["u"], t["k"], t["g_in"], t["g_out"], factors, causal=causal))
+    want = _oracle(w, nfft, causal)
+    assert rel_l2(y, want) <= (2.0 ** -9 if dtype == torch.bfloat16 else 2.0 ** -12) + 1e-6
+
+
+# Rows that are no multiple of 8 elements go through the chunk kernels in unaligned pieces, the last one shifted into place: every
+# remainder, rows that end with a chunk row or one element behind it, rows shorter than a piece, alone and in pairs
+@pytest.mark.parametrize("B", [1, 2, 3])
+@pytest.mark.parametrize("n,klen,factors", [
+    (4095, 1, (128, 64)), (4089, 4090, (128, 64)), (2057, 2049, (128, 64)), (4090, 3, (64, 128)), (2051, 8, (32, 16, 16)),
+    (4092, 15, (128, 64)), (8191, 16383, (128, 128)), (4097, 9, (128, 128)), (9, 5, (128, 64)), (7, 6, (128, 64)), (1, 7, (128, 128)),
+    (8189, 8195, (32, 32, 16)),
+])
+def test_bf16_chunks_rows_of_any_length(mm, B, n, klen, factors):
+    announce("conv bf16 chunks, any row length", B, n, klen, factors)
+    nfft = int(np.prod(factors))
+    w = workloads.conv_inputs(B, 3, n, seed=n + klen, gates="normal", bf16=True)
+    k = np.random.default_rng(klen).standard_normal((3, klen)) / np.sqrt(klen)
+    w["k"] = torch.from_numpy(k).to(torch.bfloat16).float().numpy()
+    guard = torch.full((B * 3 * n + 64,), 7.0, device="cuda", dtype=torch.bfloat16)   # nothing past the result is written
+    y = host(mm.monarch_causal_conv(dev(w["u"], True), dev(w["k"], True), dev(w["g_in"], True), dev(w["g_out"], True), factors,
+                                    causal=False, out=guard[:B * 3 * n].view(B, 3, n)))
+    assert rel_l2(y, _oracle(w, nfft, False)) <= TOL_BF16
+    assert (guard[B * 3 * n:] == 7.0).all()
