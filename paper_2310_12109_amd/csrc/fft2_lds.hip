@@ -1036,33 +1036,27 @@ static int launch_modes(const Fft2Args &p, hipStream_t s)
         return launch_one<F1, F2, false, LD_C16, ST_C32_NATURAL>(p, s);
     if (p.O == 1 && p.inverse && p.load == LD_C32_CONJ && p.store == ST_CPLX_CONJ_SCALE)   // monarch_ifft, complex bf16 rows
         return launch_one<F1, F2, true, LD_C32_CONJ, ST_CPLX_CONJ_SCALE>(p, s);
-    if (!p.inverse && p.store != ST_C16) {   // whole convolution in one kernel
-        if (p.load == LD_REAL_PAIR && p.store == ST_REAL_PAIR) return launch_one<F1, F2, false, LD_REAL_PAIR, ST_REAL_PAIR>(p, s);
-        if (p.load == LD_REAL && p.store == ST_REAL_SCALE_GATE) return launch_one<F1, F2, false, LD_REAL, ST_REAL_SCALE_GATE>(p, s);
-        return fail(MONARCH_EINVAL, "internal: fused chunk convolution modes %d/%d not built", p.load, p.store);
+    // Convolutions of two factors come with one split per length: whole rows in one kernel, the spectrum of k; channels in pairs
+    // (both spectra first, then the inverse) from 8192 on.
+    constexpr bool rows = (F1 == F2 && F1 >= 32) || (F1 == 128 && F2 == 64), pairs = F1 == 128 && F2 >= 64;
+    if constexpr (rows) {
+        if (!p.inverse && p.load == LD_REAL_PAIR && p.store == ST_REAL_PAIR) return launch_one<F1, F2, false, LD_REAL_PAIR, ST_REAL_PAIR>(p, s);
+        if (!p.inverse && p.load == LD_REAL && p.store == ST_REAL_SCALE_GATE) return launch_one<F1, F2, false, LD_REAL, ST_REAL_SCALE_GATE>(p, s);
+        if (!p.inverse && p.load == LD_REAL && p.store == ST_C16) return launch_one<F1, F2, false, LD_REAL, ST_C16>(p, s);
     }
-    if (!p.inverse) {
-        switch (p.load) {
-        case LD_REAL: return launch_one<F1, F2, false, LD_REAL, ST_C16>(p, s);
-        case LD_REAL_PAIR: return launch_one<F1, F2, false, LD_REAL_PAIR, ST_C16>(p, s);
-        case LD_C16: return launch_one<F1, F2, false, LD_C16, ST_C16>(p, s);
-        default: break;
-        }
-    } else if (p.load == LD_C16_CONJ_MULK) {
-        switch (p.store) {
-        case ST_REAL_SCALE_GATE: return launch_one<F1, F2, true, LD_C16_CONJ_MULK, ST_REAL_SCALE_GATE>(p, s);
-        case ST_REAL_PAIR: return launch_one<F1, F2, true, LD_C16_CONJ_MULK, ST_REAL_PAIR>(p, s);
-        case ST_C16: return launch_one<F1, F2, true, LD_C16_CONJ_MULK, ST_C16>(p, s);
-        default: break;
-        }
-    } else if (p.load == LD_C16_HERM_MULK) {
-        if (p.store == ST_C16) {
-            // three factors and room for two tiles: mirror chunks together
-            if (p.O >= 2 && p.O % 2 == 0 && lds_bytes(F1, F2, 2) + 1024 <= 80 * 1024)
-                return launch_vec<F1, F2, true, LD_C16_HERM_MULK, ST_C16, true, true>(p, s);
-            return launch_one<F1, F2, true, LD_C16_HERM_MULK, ST_C16>(p, s);
-        }
-        if (p.store == ST_REAL_PAIR) return launch_one<F1, F2, true, LD_C16_HERM_MULK, ST_REAL_PAIR>(p, s);
+    if constexpr (pairs) {
+        if (!p.inverse && p.load == LD_REAL_PAIR && p.store == ST_C16) return launch_one<F1, F2, false, LD_REAL_PAIR, ST_C16>(p, s);
+        if (p.inverse && p.load == LD_C16_HERM_MULK && p.store == ST_REAL_PAIR) return launch_one<F1, F2, true, LD_C16_HERM_MULK, ST_REAL_PAIR>(p, s);
+    }
+    if (p.store != ST_C16) return fail(MONARCH_EINVAL, "internal: chunk kernel modes %d/%d not built", p.load, p.store);
+    // chunks of three factors
+    if (!p.inverse && p.load == LD_C16) return launch_one<F1, F2, false, LD_C16, ST_C16>(p, s);
+    if (p.inverse && p.load == LD_C16_CONJ_MULK) return launch_one<F1, F2, true, LD_C16_CONJ_MULK, ST_C16>(p, s);
+    if (p.inverse && p.load == LD_C16_HERM_MULK) {
+        // room for two tiles: mirror chunks together
+        if (p.O >= 2 && p.O % 2 == 0 && lds_bytes(F1, F2, 2) + 1024 <= 80 * 1024)
+            return launch_vec<F1, F2, true, LD_C16_HERM_MULK, ST_C16, true, true>(p, s);
+        return launch_one<F1, F2, true, LD_C16_HERM_MULK, ST_C16>(p, s);
     }
     return fail(MONARCH_EINVAL, "internal: chunk kernel modes %d/%d not built", p.load, p.store);
 }
