@@ -285,8 +285,8 @@ __device__ __forceinline__ void unpack8(const u32x4 &w, float (&v)[8])
 // A piece of 8 neighbouring elements of a real row of n, elements e ... e + 7, e a multiple of 8.  Rows of any length but a multiple
 // of 8 start anywhere (PIECES == false): their pieces are unaligned 16-byte accesses.  The row's last piece is then loaded from
 // its last 8 elements, so that nothing past the tensor is touched, and shifted into place by piece_in_place, where the loads
-// have arrived; rows shorter than 8 are read element by element.  (Element by element for every row: 3.5 times as slow,
-// 271 -> 125 us for 6144 rows of 4087.)
+// have arrived; rows shorter than 8 are read element by element.  (Element by element, with the
+// rows through memory: 271 us for 6144 rows of 4087, in pieces 132, rows of 4088 116.)
 typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 template <bool PIECES> __device__ __forceinline__ u32x4 load_piece(const bf16_t *row, int e, int n)
 {
