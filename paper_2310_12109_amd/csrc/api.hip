@@ -988,8 +988,12 @@ static int conv_run(const void *u, const void *k, const void *g_in, const void *
     // entries of a batch apart, and pays for it with twice the transforms.
     const bool mfma_split = fft_mfma_supported(nfft, factors, nf, dt);
     const int per = mfma_split || fft_mfma_f32_supported(nfft, factors, nf, dt) ? 2 : 1;
+    // Two factors that are no chunk keep the kernel that is fp32 throughout at any number of rows: their passes hold the spectrum of k in
+    // fp32, and a chunk's spectrum in bf16 is further off 64 bits (16 x 64 4.6e-3 : 32 x 32 5.0e-3).  In place of three factors it is nearer (16 x 16 x 32
+    // 5.8e-3 : 128 x 64 4.6e-3).
+    const bool chunk_split = mfma_split && (nf == 3 || conv_chunks_supported(factors, nf, dt));
     static const int two_factors[][2] = {{16, 16}, {32, 32}, {64, 32}, {64, 64}, {128, 64}, {128, 128}};
-    if (mfma_split && !conv_fused_path(n, klen, factors, nf, dt))   // bf16: the split that the kernels of one or two launches are built for
+    if (chunk_split && !conv_fused_path(n, klen, factors, nf, dt))   // bf16: the split that the kernels of one or two launches are built for
         for (const auto &f : two_factors)
             if (f[0] * f[1] == nfft) {
                 factors = f;
@@ -1000,7 +1004,7 @@ static int conv_run(const void *u, const void *k, const void *g_in, const void *
     if (fused == 1) return launch_conv_mfma_2048(u, k, g_in, g_out, y, B, H, n, klen, dt, s);
     if (fused == 2) return launch_conv_mfma_256(u, k, g_in, g_out, y, B, H, n, klen, s);
     if (fused == 3) return launch_conv_mfma_16k(u, k, g_in, g_out, y, B, H, n, klen, s);
-    if (conv_fft_supported(nfft) && !(mfma_split && conv_chunks_faster(B, H, n, klen, nfft)))
+    if (conv_fft_supported(nfft) && !(chunk_split && conv_chunks_faster(B, H, n, klen, nfft)))
         return launch_conv_fft(u, k, g_in, g_out, y, B, H, n, klen, nfft, per, dt, s);
 
     const size_t buf = align_up(rows * nfft * sizeof(float2), 256);

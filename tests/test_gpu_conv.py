@@ -343,6 +343,10 @@ def test_fp32_other_splits_keep_rows_apart(mm, factors):
     (1, 4, 2047, 2047, (16, 16, 16), "normal", True, torch.bfloat16),
     (2, 3, 2048, 4096, (4, 1024), "normal", False, torch.bfloat16),
     (3, 2, 4095, 4095, (4, 2048), "normal", True, torch.float16),
+    # two factors that are no chunk, with as many rows as send the others to the chunk kernels
+    (2, 3072, 40, 40, (64, 16), "normal", True, torch.bfloat16),
+    (3, 512, 48, 48, (128, 32), "normal", True, torch.bfloat16),
+    (3, 4, 1000, 1000, (16, 128), "normal", True, torch.bfloat16),
 ])
 def test_16_bit_rows_in_registers(mm, B, H, n, klen, factors, gates, causal, dtype):
     announce("conv 16-bit rows in registers", B, H, n, klen, factors, gates, causal, dtype)
