@@ -293,10 +293,12 @@ template <bool PIECES> __device__ __forceinline__ u32x4 load_piece(const bf16_t 
     if constexpr (PIECES) return *reinterpret_cast<const u32x4 *>(row + (e < n ? e : 0));   // past the row: any valid address, the value is dropped
     else if (n >= 8) return *reinterpret_cast<const u32x4_any *>(row + (e <= n - 8 ? e : n - 8));
     u32x4 w = {0, 0, 0, 0};
-    const uint16_t *bits = reinterpret_cast<const uint16_t *>(row);
+    if (e == 0) {   // (one piece holds the row: the other threads ask for nothing)
+        const uint16_t *bits = reinterpret_cast<const uint16_t *>(row);
 #pragma unroll
-    for (int t = 0; t < 7; ++t)
-        if (t < n) w[t / 2] |= (uint32_t)bits[t] << (16 * (t & 1));
+        for (int t = 0; t < 7; ++t)
+            if (t < n) w[t / 2] |= (uint32_t)bits[t] << (16 * (t & 1));
+    }
     return w;
 }
 template <bool PIECES> __device__ __forceinline__ void piece_in_place(u32x4 &w, int e, int n)
