@@ -745,11 +745,18 @@ static int conv_chunks_lds(const void *u, const void *k, const void *g_in, const
 {
     // rows that share a complex row: two batch entries of a channel, or (one sequence per channel) two
     // neighbouring channels, then with the kernels paired alike and separated again before the inverse.  With two factors
-    // that costs a launch and the rows between them, so channels stay alone (4096: H = 768 21 : 30 us, 3072 53 : 57; 8192: H = 256
-    // 20 : 40, 768 44 : 53, 1536 77 : 79) but where the workgroups, one per compute unit from 8192 on, have many rounds
-    // of rows to go, which pairs halve (8192: H = 1024 55 : 53, 3072 142 : 121; 16384: H = 1024 110 : 107, 1536 158 : 173, 3072 317 : 300).
-    const int rounds = (H + 255) / 256;
-    const bool pairs_pay = nf == 3 || (nfft >= 8192 && n % 8 == 0 && (rounds == 4 || rounds > 6));
+    // that costs a launch and the rows between them, so channels stay alone as long as the workgroups, one per compute unit from 8192 on,
+    // have few rounds of rows to go: up to three (us, alone : in pairs, 4096: H = 768 21 : 30, 3072 53 : 57; 8192: H = 256 20 : 40, 768
+    // 44 : 53).  From four rounds on pairs, which halve them, take as long or less but for 6 rounds (8192: H = 1024 55 : 53, 1536 77 : 79,
+    // 3072 142 : 121; 16384: 110 : 107, 158 : 173, 317 : 300); the line is one, so that a longer call is not another kind of call again.
+    // Rows of no multiple of 8 stay alone: pairs of them were timed element by element only, which takes twice the time of pieces.
+    bool pairs_pay = nf == 3;
+    if (nf == 2 && B == 1 && nfft >= 8192 && n % 8 == 0) {
+        int dev = 0, ncu = 0;
+        MONARCH_HIP_CHECK(hipGetDevice(&dev));
+        MONARCH_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+        pairs_pay = H > 3 * ncu;
+    }
     const bool by_channel = pairs_pay && B == 1 && H >= 2;
     const bool paired = B >= 2 || by_channel;
     const int pair_stride = by_channel ? 1 : H;

@@ -24,3 +24,19 @@ for factors in [(16, 32), (32, 16), (16, 64), (64, 16), (16, 128), (128, 16), (3
 """)
     for kernels in got:
         assert len(kernels) == 1 and kernels[0].startswith("conv_kernel "), kernels
+
+
+# one sequence per channel, two factors: channels alone up to three rounds of rows for every compute unit, in pairs beyond, at one line
+@pytest.mark.parametrize("units", [256, 304, 64])
+def test_channels_alone_or_in_pairs(recorded, units):
+    got = recorded(f"""
+calls.compute_units({units})
+result = [[H, n, factors[1], calls.conv(1, H, n, klen, factors)] for factors, n, klen in
+          [((128, 64), 4096, 4096), ((128, 64), 48, 8192), ((128, 64), 4095, 4095), ((128, 128), 8192, 16384), ((128, 128), 9, 9)]
+          for H in list(range(1, 40)) + [{units} * r + d for r in range(1, 17) for d in (-1, 0, 1)]]
+""")
+    for H, n, f, kernels in got:
+        if n % 8 == 0 and H > 3 * units:
+            assert len(kernels) == 3 and kernels[2].startswith(f"fft2_lds_kernel 128 {f} 1 8 6"), (H, n, kernels)
+        else:
+            assert len(kernels) == 2 and kernels[1].startswith(f"fft2_lds_kernel 128 {f} 0 3 3"), (H, n, kernels)
