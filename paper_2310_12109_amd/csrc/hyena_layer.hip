@@ -73,13 +73,16 @@ static rocblas_handle blas_handle()
 }
 
 // C (row-major, per batch entry) = op over row-major operands, as one strided-batched GEMM in rocBLAS's
-// column-major terms.  All of type dt, fp32 accumulation.
-static int gemm(rocblas_handle h, rocblas_operation ta, rocblas_operation tb, int m, int n, int k, const void *a, int lda,
+// column-major terms, on stream s.  All of type dt, fp32 accumulation.  The handle is the device's, so its stream is
+// set and the product enqueued under one lock: another thread would send it to its own stream in between.
+static int gemm(rocblas_handle h, hipStream_t s, rocblas_operation ta, rocblas_operation tb, int m, int n, int k, const void *a, int lda,
                 int64_t sa, const void *b, int ldb, int64_t sb, float beta, void *c, int ldc, int64_t sc, int batch,
                 monarch_dtype dt)
 {
     const float alpha = 1.0f;
     const rocblas_datatype t = dt == MONARCH_F32 ? rocblas_datatype_f32_r : rocblas_datatype_bf16_r;
+    std::lock_guard<std::mutex> lock(g_blas_mutex);
+    if (g_blas.set_stream(h, s) != rocblas_status_success) return fail(MONARCH_EHIP, "rocblas_set_stream failed");
     const rocblas_status st = g_blas.gemm(h, ta, tb, m, n, k, &alpha, a, t, lda, sa, b, t, ldb, sb, &beta, c, t, ldc, sc, c, t, ldc,
                                           sc, batch, rocblas_datatype_f32_r, rocblas_gemm_algo_standard, 0, 0);
     if (st != rocblas_status_success) return fail(MONARCH_EHIP, "rocBLAS GEMM failed with status %d", (int)st);
@@ -228,7 +231,6 @@ static int run(const void *u, const void *W_in, const void *b_in, const void *k_
 {
     rocblas_handle h = blas_handle();
     if (!h) return MONARCH_EHIP;
-    if (g_blas.set_stream(h, s) != rocblas_status_success) return fail(MONARCH_EHIP, "rocblas_set_stream failed");
     const size_t es = sizeof(T);
     const int64_t plane = (int64_t)B * d * n;              // one (B, d, n) tensor
     char *base = (char *)ws;
@@ -243,7 +245,7 @@ static int run(const void *u, const void *W_in, const void *b_in, const void *k_
     //    (measured in one session at B = 8, n = 1024, d = 768: fp32 401 against 422 us per layer, bf16 109 against 103 us)
     const int parts = dt == MONARCH_F32 ? 1 : 3;
     for (int i = 0; i < parts; ++i) {
-        int rc = gemm(h, rocblas_operation_transpose, rocblas_operation_none, n, 3 * d / parts, d, u, d, (int64_t)n * d,
+        int rc = gemm(h, s, rocblas_operation_transpose, rocblas_operation_none, n, 3 * d / parts, d, u, d, (int64_t)n * d,
                       (const T *)W_in + (int64_t)i * d * d, d, 0, 0.0f, proj + (int64_t)i * d * n, n, (int64_t)3 * d * n, B, dt);
         if (rc) return rc;
     }
@@ -298,7 +300,7 @@ static int run(const void *u, const void *W_in, const void *b_in, const void *k_
         MONARCH_HIP_CHECK(hipGetLastError());
         beta = 1.0f;
     }
-    return gemm(h, rocblas_operation_transpose, rocblas_operation_transpose, d, n, d, W_out, d, 0, o, n, (int64_t)d * n, beta, y, d,
+    return gemm(h, s, rocblas_operation_transpose, rocblas_operation_transpose, d, n, d, W_out, d, 0, o, n, (int64_t)d * n, beta, y, d,
                 (int64_t)n * d, B, dt);
 }
 

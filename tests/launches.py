@@ -86,6 +86,6 @@ class Calls:
 
 
 if __name__ == "__main__":
-    scope = {"calls": Calls(sys.argv[1])}
+    scope = {"calls": Calls(sys.argv[1]), "GAP": GAP}
     exec(compile(sys.stdin.read(), "script", "exec"), scope)
     print(json.dumps(scope["result"]))

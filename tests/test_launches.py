@@ -40,3 +40,23 @@ result = [[H, n, factors[1], calls.conv(1, H, n, klen, factors)] for factors, n,
             assert len(kernels) == 3 and kernels[2].startswith(f"fft2_lds_kernel 128 {f} 1 8 6"), (H, n, kernels)
         else:
             assert len(kernels) == 2 and kernels[1].startswith(f"fft2_lds_kernel 128 {f} 0 3 3"), (H, n, kernels)
+
+
+# threads with a stream each: the products of a call go to its stream, though the threads share the device's rocBLAS handle
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_products_of_threads_go_to_their_own_streams(recorded, dtype):
+    products, launched = recorded(f"""
+import threading
+def work(t):
+    for _ in range(25):
+        calls.hyena(2, 64, 8, 3, 64, (8, 16), 1, "{dtype}", base=GAP * (1 + 16 * t), stream=1000 + t)
+threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+for t in threads: t.start()
+for t in threads: t.join()
+log = calls.log()
+result = [[[int(line[5].split()[0]) // (16 * GAP), int(line[-1])] for line in log if line[0] == "product"],
+          [int(line[-1]) for line in log if line[0] == "kernel"]]
+""")
+    assert len(products) >= 4 * 25 * 2
+    assert all(stream == 1000 + thread for thread, stream in products)
+    assert all(1000 <= stream < 1004 for stream in launched)
