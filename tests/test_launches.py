@@ -60,3 +60,34 @@ result = [[[int(line[5].split()[0]) // (16 * GAP), int(line[-1])] for line in lo
     assert len(products) >= 4 * 25 * 2
     assert all(stream == 1000 + thread for thread, stream in products)
     assert all(1000 <= stream < 1004 for stream in launched)
+
+
+# what rocBLAS is asked to read and write lies inside the caller's tensors and scratch, to the last element, at the smallest and
+# the largest calls; C is written by no two entries of a batch
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,n,d,factors,head_dim", [
+    (1, 8, 8, (16, 16), 1), (3, 128, 48, (16, 16), 16), (8, 1024, 768, (64, 32), 16), (8, 1024, 768, (64, 32), 1), (64, 128, 768, (16, 16), 1),
+    (4, 2048, 768, (64, 64), 16), (32, 1024, 768, (64, 32), 16), (64, 1536, 768, (64, 64), 1), (19, 1240, 384, (64, 64), 4),
+])
+def test_products_stay_inside_their_tensors(recorded, B, n, d, factors, head_dim, dtype):
+    base, gap = 1 << 38, 1 << 38
+    ws_bytes, log = recorded(f"""
+ws = calls.hyena({B}, {n}, {d}, 3, {n}, {factors}, {head_dim}, "{dtype}", base={base}, gap={gap})
+result = [ws, [line[1:] for line in calls.log() if line[0] == "product"]]
+""")
+    es = 4 if dtype == "f32" else 2
+    size = dict(enumerate([B * n * d * es, 3 * d * d * es, 3 * d * es, 9 * d * es, d // head_dim * n * es, d * d * es, d * es, B * n * d * es, ws_bytes]))
+    plain, written = 111, 0
+    assert len(log) == (2 if dtype == "f32" else 4)
+    for ops, mnk, *operands, batch, _type, _stream in log:
+        (ta, tb), (m, cols, k), batch = map(int, ops.split()), map(int, mnk.split()), int(batch)
+        shapes = [(m, k) if ta == plain else (k, m), (k, cols) if tb == plain else (cols, k), (m, cols)]
+        for (rows, columns), operand in zip(shapes, operands):
+            at, ld, stride = map(int, operand.split())
+            assert ld >= rows and stride >= 0
+            end = at + (stride * (batch - 1) + ld * (columns - 1) + rows) * es
+            tensor = (at - base) // gap
+            assert end <= base + gap * tensor + size[tensor], (operand, rows, columns)
+        assert batch == 1 or stride >= ld * (columns - 1) + rows
+        written += m * cols * batch
+    assert written == 4 * B * n * d
