@@ -300,3 +300,15 @@ def test_mlp_rejects_bad_arguments(lib):
     # order 2, bf16: the two d_mid-wide intermediates; fp32: the hidden activations
     assert lib.monarch_mlp_workspace_bytes(16, 768, 3072, 4, 2, 0, 0, 1) >= 2 * 16 * 768 * 2
     assert lib.monarch_mlp_workspace_bytes(16, 768, 3072, 4, 2, 0, 0, 0) >= 16 * 3072 * 4
+
+
+def test_current_stream_with_and_without_the_private_names(monkeypatch):
+    import types
+
+    import torch
+    from paper_2310_12109_amd import binding
+    names = types.SimpleNamespace(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda device: 100 + device)
+    assert binding._stream_lookup(names)() == 103
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    for missing in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        assert binding._stream_lookup(types.SimpleNamespace(**{k: v for k, v in vars(names).items() if k != missing}))() == 77
