@@ -30,6 +30,8 @@ extern "C" {
 void recorder_reset() { std::lock_guard<std::mutex> lock(g_mutex); g_log.clear(); }
 int recorder_count() { return (int)g_log.size(); }
 const char *recorder_line(int i) { return g_log[i].c_str(); }
+int recorder_built_count() { return (int)g_names.size(); }   // kernels of the library
+const char *recorder_built(int i) { auto it = g_names.begin(); std::advance(it, i); return it->second.c_str(); }
 void recorder_compute_units(int n) { g_units = n; }
 
 void **__hipRegisterFatBinary(const void *) { static void *handle; return &handle; }

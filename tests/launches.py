@@ -42,12 +42,17 @@ class Calls:
     def __init__(self, so):
         self.rec = ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL)
         self.rec.recorder_line.restype = ctypes.c_char_p
+        self.rec.recorder_built.restype = ctypes.c_char_p
         self.lib = ctypes.CDLL(LIB)
         self.lib.monarch_last_error.restype = ctypes.c_char_p
         self.lib.monarch_hyena_heads_layer_workspace_bytes.restype = ctypes.c_size_t
 
     def compute_units(self, n):
         self.rec.recorder_compute_units(n)
+
+    def built(self):
+        """Every kernel of the library, as kernels() names them."""
+        return [plain(self.rec.recorder_built(i).decode()) for i in range(self.rec.recorder_built_count())]
 
     def log(self):
         lines = [self.rec.recorder_line(i).decode().split("\t") for i in range(self.rec.recorder_count())]
@@ -68,8 +73,18 @@ class Calls:
         if static:
             rc = self.lib.monarch_causal_conv_static(*args, ctypes.c_void_p(stream))
         else:
-            rc = self.lib.monarch_causal_conv(*args, ws, ctypes.c_size_t(GAP - 1), ctypes.c_void_p(stream))
+            rc = self.lib.monarch_causal_conv(*args, ws, ctypes.c_size_t(GAP), ctypes.c_void_p(stream))
         assert rc == 0, (self.lib.monarch_last_error(), B, H, n, klen, factors, dtype)
+        return self.kernels()
+
+    def fft(self, rows, factors, dtype="bf16", real=1, inverse=0):
+        nfft = 1
+        for f in factors:
+            nfft *= f
+        call = self.lib.monarch_ifft if inverse else self.lib.monarch_fft
+        rc = call(ctypes.c_void_p(GAP), ctypes.c_void_p(2 * GAP), ctypes.c_int64(rows), nfft, (ctypes.c_int * len(factors))(*factors), len(factors),
+                  real, DTYPES[dtype], ctypes.c_void_p(3 * GAP), ctypes.c_size_t(GAP - 1), None)
+        assert rc == 0, (self.lib.monarch_last_error(), rows, factors, dtype)
         return self.kernels()
 
     def hyena(self, B, n, d, taps, klen, factors, head_dim, dtype, base=GAP, gap=GAP, stream=0):

@@ -91,3 +91,28 @@ result = [ws, [line[1:] for line in calls.log() if line[0] == "product"]]
         assert batch == 1 or stride >= ld * (columns - 1) + rows
         written += m * cols * batch
     assert written == 4 * B * n * d
+
+
+# every convolution and transform finds its kernels, and every instance of the chunk kernels that is built is one that some call takes:
+# all splits into two and three factors of 16 ... 128 and others, rows of every kind, few and many
+def test_every_call_reaches_a_built_chunk_kernel_and_every_chunk_kernel_is_reached(recorded):
+    unreached = recorded("""
+import itertools
+splits = [f for nf in (2, 3) for f in itertools.product((8, 16, 32, 64, 128, 256), repeat=nf)]
+seen = set()
+for f in splits:
+    nfft = 1
+    for v in f: nfft *= v
+    if nfft > 1 << 18: continue
+    for rows in (1, 3, 5000):
+        for real in (0, 1):
+            for inverse in (0, 1):
+                seen.update(calls.fft(rows, f, "bf16", real, inverse))
+    for B, H in ((1, 1), (1, 6), (1, 4000), (2, 3), (3, 3072)):
+        for n, klen in ((nfft // 2, nfft // 2), (nfft // 2 - 3, nfft // 2 - 3), (nfft, nfft), (nfft // 2, 9), (7, 16), (nfft - 8, nfft - 5)):
+            for gates in (0, 3):
+                for dtype in ("bf16", "f16", "f32"):
+                    seen.update(calls.conv(B, H, n, klen, f, dtype, gates=gates))
+result = sorted(k for k in calls.built() if k.startswith(("fft2_lds_kernel", "conv3_middle_kernel")) and k not in seen)
+""")
+    assert unreached == []
