@@ -81,23 +81,24 @@ def test_ragged_shapes_fp32(mm, B, H, n, klen, factors, gates):
 
 @pytest.mark.parametrize("B,H,n,klen,factors,gates", [
     (3, 5, 100, 37, (16, 16), "normal"),          # odd batch: the last row of each channel travels alone
-    (1, 3, 128, 128, (16, 16), "normal"),         # B = 1: no pairing
+    (1, 3, 128, 128, (16, 16), "normal"),         # B = 1
     (2, 3, 1000, 999, (32, 64), "none"),
     (5, 2, 2048, 2048, (64, 64), "normal"),
     (4, 3, 1024, 300, (128, 16), "normal"),
-    (3, 2, 2000, 2000, (16, 16, 16), "normal"),   # three factors
+    (3, 2, 2000, 2000, (16, 16, 16), "normal"),   # three factors of a length that two are taken for
     (2, 2, 4096, 4096, (32, 16, 64), "normal"),   # nfft = 8n
-    (1, 5, 1000, 999, (32, 64), "normal"),        # B = 1: neighbouring channels share a complex row; H odd
-    (1, 4, 2048, 2048, (16, 16, 16), "normal"),   # the same with three factors: every chunk stage in one kernel
-    (1, 5, 16384, 16000, (32, 32, 32), "normal"), # ... H odd: the last channel travels alone
+    (1, 5, 1000, 999, (32, 64), "normal"),        # B = 1, klen odd; H odd
+    (1, 4, 2048, 2048, (16, 16, 16), "normal"),
+    (1, 5, 16384, 16000, (32, 32, 32), "normal"), # three factors, B = 1: neighbouring channels share a complex row, every chunk
+                                                  # stage in one kernel; H odd: the last channel travels alone
     (1, 3, 8000, 5000, (16, 64, 32), "normal"),   # ... unequal chunk factors, nfft > 2n
     (1, 2, 30000, 30000, (64, 32, 32), "none"),
-    (3, 3, 8192, 8000, (32, 32, 16), "normal"),   # three factors, B > 1: batch entries paired at a stride of H = 3 rows, odd B
-    (2, 2, 12288, 12288, (64, 16, 32), "normal"), # ... first factor 64, nfft > 2n
+    (3, 3, 8192, 8000, (32, 32, 16), "normal"),   # B > 1: batch entries paired at a stride of H = 3 rows, odd B
+    (2, 2, 12288, 12288, (64, 16, 32), "normal"), # three factors that end in no chunk: passes, nfft > 2n
     (1, 2, 3000, 17, (128, 64), "none"),          # short kernel, no gates
 ])
 def test_ragged_shapes_bf16_matrix_core_passes(mm, B, H, n, klen, factors, gates):
-    announce("conv bf16 mfma passes", B, H, n, klen, factors, gates)
+    announce("conv bf16 ragged", B, H, n, klen, factors, gates)
     nfft = int(np.prod(factors))
     w = workloads.conv_inputs(B, H, n, seed=n + klen + 1, gates=gates, bf16=True)
     w["k"] = np.ascontiguousarray(w["k"][:, :klen])
@@ -381,3 +382,47 @@ def test_bf16_chunks_rows_of_any_length(mm, B, n, klen, factors):
                                     causal=False, out=guard[:B * 3 * n].view(B, 3, n)))
     assert rel_l2(y, _oracle(w, nfft, False)) <= TOL_BF16
     assert (guard[B * 3 * n:] == 7.0).all()
+
+
+# the chunk kernels where many rows take them: whole rows of 1024 and 4096 (short rows, so that the direct sum stays cheap), alone and in
+# pairs of batch entries, rows of any length, past half the transform (4096); channels alone and in pairs on both sides of the
+# line (three rows for each of 256 compute units), an odd number of them, ragged rows, kernels longer than the rows
+@pytest.mark.parametrize("B,H,n,klen,factors", [
+    (2, 3072, 40, 40, (32, 32)), (1, 3073, 48, 17, (32, 32)), (5, 1024, 8, 100, (32, 32)),
+    (3, 512, 41, 9, (64, 64)), (3, 513, 48, 48, (64, 64)), (1, 1025, 39, 64, (64, 64)), (2, 512, 2051, 3, (64, 64)), (1, 1024, 64, 8, (64, 64)),
+    (1, 768, 48, 48, (128, 64)), (1, 769, 48, 50, (128, 64)), (1, 1601, 64, 9, (128, 64)), (1, 770, 648, 5, (128, 64)), (1, 900, 47, 6, (128, 64)),
+    (1, 1000, 48, 41, (128, 128)), (1, 1601, 56, 3, (128, 128)), (1, 769, 1160, 4, (128, 128)),
+])
+@pytest.mark.parametrize("gates", ["normal", "none"])
+def test_bf16_chunks_many_rows(mm, B, H, n, klen, factors, gates):
+    announce("conv bf16 chunks, many rows", B, H, n, klen, factors, gates)
+    nfft = int(np.prod(factors))
+    w = workloads.conv_inputs(B, H, n, seed=n + klen + H, gates=gates, bf16=True)
+    k = np.random.default_rng(klen).standard_normal((H, klen)) / np.sqrt(klen)
+    w["k"] = torch.from_numpy(k).to(torch.bfloat16).float().numpy()
+    y = _run(mm, w, factors, True, False)
+    want = _oracle(w, nfft, False)
+    assert rel_l2(y, want) <= TOL_BF16
+    # every row by itself against the larger of the two that share a transform: one bf16 error of the transform is in both
+    num, den = np.linalg.norm(y - want, axis=2), np.linalg.norm(want, axis=2)
+    assert (num <= 2.5 * TOL_BF16 * den.max()).all()
+
+
+# three factors beyond 16384: every chunk shape, batch entries in pairs (six launches), an odd batch, rows that end inside a row
+# of a chunk; one sequence per channel in the shapes that have no fused middle
+@pytest.mark.parametrize("B,H,n,klen,factors", [
+    (3, 3, 700, 300, (32, 32, 32)), (2, 2, 16384, 900, (32, 32, 32)), (3, 2, 701, 65, (64, 64, 32)), (2, 3, 700, 300, (16, 32, 64)),
+    (5, 2, 333, 77, (16, 64, 64)), (3, 3, 700, 300, (128, 16, 16)), (2, 3, 700, 300, (16, 128, 64)), (3, 2, 700, 300, (16, 64, 128)),
+    (3, 2, 700, 300, (16, 128, 128)), (1, 1, 700, 300, (32, 32, 32)),
+    (1, 3, 700, 300, (16, 128, 64)), (1, 4, 701, 33, (16, 64, 128)), (1, 3, 9000, 300, (16, 128, 128)),
+])
+def test_bf16_three_factor_chunks(mm, B, H, n, klen, factors):
+    announce("conv bf16 chunks, three factors", B, H, n, klen, factors)
+    nfft = int(np.prod(factors))
+    w = workloads.conv_inputs(B, H, n, seed=n + klen, gates="normal", bf16=True)
+    w["k"] = np.ascontiguousarray(w["k"][:, :klen])
+    y = _run(mm, w, factors, True)
+    want = _oracle(w, nfft)
+    assert rel_l2(y, want) <= TOL_BF16
+    num = np.linalg.norm((y - want).reshape(-1, n), axis=1)
+    assert (num / np.linalg.norm(want.reshape(-1, n), axis=1)).max() <= 2.5 * TOL_BF16

@@ -27,8 +27,9 @@ def _static_call(lib, t, y, factors, causal=1):
 
 @pytest.mark.parametrize("bf16,factors,shapes", [
     (True, (128, 64), [(4, 8, 4096), (2, 3, 2048), (1, 2, 1000)]),       # LDS-chunk path: spectrum of k in scratch
-    (False, (32, 64), [(5, 7, 1000), (2, 3, 512)]),                      # fp32 matrix-core passes: row buffers + k_f
-    (True, (16, 16, 32), [(3, 6, 4096), (1, 4, 1500)]),                  # three factors
+    (False, (32, 64), [(5, 7, 1000), (2, 3, 512)]),                      # fp32, rows in registers
+    (True, (16, 16, 32), [(3, 6, 4096), (1, 4, 1500)]),                  # three factors of a length that two are taken for
+    (True, (32, 32, 32), [(3, 3, 2000), (1, 4, 1500), (2, 2, 333)]),     # three factors: row buffers + k_f, six launches and four
     (False, (10, 12), [(3, 4, 50), (1, 1, 7)]),                          # generic fp32 passes
 ])
 def test_static_scratch_calls_in_a_row_match_the_workspace_entry_point(bf16, factors, shapes):
