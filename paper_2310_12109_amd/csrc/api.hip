@@ -960,6 +960,7 @@ static int conv_passes_mfma(const void *u, const void *k, const void *g_in, cons
 //   4096     14 : 17   18 : 17    21 : 21    35 : 29    62 : 45                (half)
 //   4096     14 : 17   24 : 17    31 : 22    47 : 29    82 : 46                (not half; c = 256 15 : 17)
 //   8192     21 : 20   60 : 29   104 : 47   174 : 71   313 : 116               (32 values of a row per thread)
+// 512 (37 x 384 rows of 136: 21, in passes through memory 47) and 256 beyond 128 positions, not timed by itself, have no chunk of their own here.
 static bool conv_chunks_faster(int B, int H, int n, int klen, int nfft)
 {
     const int64_t c = ((int64_t)B + 1) / 2 * H;

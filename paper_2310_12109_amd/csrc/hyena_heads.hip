@@ -258,6 +258,8 @@ static int run(const void *proj, void *x12v, void *o, const void *k_short, const
 // parts the table and what lies between (d_h = 10: n = 1024 684 : 521, 2048 663 : 653; 7: 512 591 : 515; 6: 256 518 : 475;
 // 5: 128 111 : 109, 256 377 : 377); at B = 1 the line lies a little lower (8: 1024 111 : 128, 12: 2048 187 : 205).  With
 // 4 features (rows padded to 4) an earlier form gained nothing at n = 128 and lost from n = 1024 on (bf16 147 : 280).
+// (The bf16 convolutions of 512 points, n = 136 to 256, and those of 1024 and 4096 with few rows have become up to twice as fast since; the table has
+// none of them but with many rows, and the line of 5 to 7 features was not drawn again.)
 bool hyena_heads_supported(int B, int n, int d, int klen, int nfft, const int *factors, int nf, int head_dim, monarch_dtype dt)
 {
     if (conv_fft_supported(nfft) && fft_mfma_f32_supported(nfft, factors, nf, dt)) {
