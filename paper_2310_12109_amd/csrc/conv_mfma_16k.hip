@@ -47,7 +47,7 @@ constexpr int jrow(int T, int q, int kg, int r) { return 64 * T + 32 * (r >> 1) 
 // Per-lane constant A operands of the tiles T = 0: [lane][q][re, im][word h]: F_128[j][8 kg + 2h], [8 kg + 2h + 1]
 // with j the tile's row for A-operand row lane % 16 (= accumulator row 4 kg' + r).  The tiles T = 1 hold the rows
 // j + 64, and F[j + 64][c] = (-1)^c F[j][c]: the same words with the sign of every odd slot (the high halves) flipped.
-struct OperandTable { uint32_t v[64][4][2][4]; };
+struct alignas(16) OperandTable { uint32_t v[64][4][2][4]; };
 constexpr OperandTable make_operands()
 {
     OperandTable t{};

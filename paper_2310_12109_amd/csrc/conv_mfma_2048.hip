@@ -84,7 +84,7 @@ template <typename E> constexpr uint32_t half_bits(double v);
 template <> constexpr uint32_t half_bits<bf16_t>(double v) { return bf16_bits(v); }
 template <> constexpr uint32_t half_bits<f16_t>(double v) { return f16_bits(v); }
 
-struct TwiddleTable { float v[N1][N2][2]; };   // unpadded in memory (16 KB); the copy in LDS has rows of TW_LD
+struct alignas(16) TwiddleTable { float v[N1][N2][2]; };   // unpadded in memory (16 KB); the copy in LDS has rows of TW_LD
 constexpr TwiddleTable make_twiddles()
 {
     TwiddleTable t{};
@@ -99,7 +99,7 @@ constexpr TwiddleTable make_twiddles()
 // Per-lane constant MFMA operands, 8 x 16 bytes per lane:
 //   [2t], [2t+1]: real / imaginary part of F64[slot][16t + lane%16]  (= F64[16t + lane%16][slot])
 //   [4+2t], [5+2t]: real / imaginary part of F32[16t + lane%16][slot]
-struct OperandTable { uint32_t v[64][8][4]; };
+struct alignas(16) OperandTable { uint32_t v[64][8][4]; };
 template <typename E>
 constexpr OperandTable make_operands()
 {
