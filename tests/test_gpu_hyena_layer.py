@@ -27,8 +27,8 @@ def _want(w, nfft, causal=True):
 
 
 @pytest.mark.parametrize("B,n,d,ks,factors,bias", [
-    (2, 1024, 64, 3, (64, 32), True),      # the long convolution on the fused 64 x 32 kernel
-    (3, 128, 48, 4, (16, 16), False),      # the fused 16 x 16 kernel, no biases, odd batch
+    (2, 1024, 64, 3, (64, 32), True),      # the long convolution with its rows in registers
+    (3, 128, 48, 4, (16, 16), False),      # the same at 256, no biases, odd batch
     (2, 200, 24, 1, (20, 20), True),       # a convolution in passes through the workspace; one-tap short kernels
     (1, 64, 8, 8, (8, 16), True),          # eight taps
 ])
@@ -78,8 +78,8 @@ def _want_heads(w, nfft, dh, causal=True):
 
 
 @pytest.mark.parametrize("B,n,d,dh,ks,factors,bias", [
-    (2, 1024, 32, 4, 3, (64, 32), True),     # 16 convolutions per head on the fused 64 x 32 kernel
-    (3, 128, 48, 16, 4, (16, 16), False),    # the paper's head dimension: 768 batch rows of three head channels
+    (2, 1024, 32, 4, 3, (64, 32), True),     # 16 convolutions per head, rows in registers
+    (3, 128, 48, 16, 4, (16, 16), False),    # the paper's head dimension: pairs of positions instead of convolutions
     (1, 200, 24, 3, 2, (20, 20), True),      # a convolution in passes through the workspace, odd head dimension
     (2, 64, 8, 8, 3, (8, 16), True),         # a single head
     (2, 64, 8, 1, 3, (8, 16), True),         # head dimension 1: the layer without heads
@@ -93,8 +93,8 @@ def test_heads_fp32(mm, B, n, d, dh, ks, factors, bias):
         np.testing.assert_array_equal(_run_heads(mm, w, factors, 1, False), _run(mm, w, factors, False))
 
 
-# (64, 32): the fused kernel forms the outer products on its loads (full rows, short rows, an odd number of batch rows);
-# (16, 16): the outer-product kernel and the library's convolution
+# (64, 32) with 3 and 4 features: the fused kernel forms the outer products on its loads (full rows, short rows, an odd number of
+# batch rows); 8 and 16 features: pairs of positions
 @pytest.mark.parametrize("B,n,d,dh,ks,factors", [(2, 1024, 64, 16, 3, (64, 32)), (3, 512, 24, 4, 3, (64, 32)), (1, 1000, 9, 3, 2, (64, 32)),
                                                  (5, 128, 40, 8, 3, (16, 16))])
 def test_heads_bf16(mm, B, n, d, dh, ks, factors):
